@@ -15,7 +15,7 @@ LIB = os.path.join(PKG, "libquick.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # -packed-fp32-ops: keep the compiler from emitting packed fp32 VALU ops.
-FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-pthread",
+FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++20", "-fPIC", "-pthread",
          "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include")]
@@ -23,7 +23,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-pthread",
 UNITS = [("quick_pack.cpp", []),
          ("quick_gemm.hip", ["-DQUICK_PART=0"]),
          ("quick_gemm.hip", ["-DQUICK_PART=1"]),
-         ("quick_gemm.hip", ["-DQUICK_PART=2"])]
+         ("quick_gemm.hip", ["-DQUICK_PART=2"]),
+         ("quick_gemm.hip", ["-DQUICK_PART=3"])]
 
 
 def _msgs(r):

@@ -51,10 +51,12 @@
 #define QUICK_HOST 1
 #define QUICK_STREAM 1
 #define QUICK_TILED 1
+#define QUICK_WSPLIT 1
 #else
 #define QUICK_HOST (QUICK_PART == 0)
 #define QUICK_STREAM (QUICK_PART == 1)
 #define QUICK_TILED (QUICK_PART == 2)
+#define QUICK_WSPLIT (QUICK_PART == 3)
 #endif
 
 namespace {
@@ -1706,6 +1708,474 @@ tiled32_kernel(const uint16_t* __restrict__ x, const u4_t* __restrict__ pw,
     }
 }
 
+// K slices from which on a wave-split launch leaves the adding of its partial
+// sums to the reduction pass (see the kernel).
+[[maybe_unused]] constexpr int kWsReduceSplit = 4;
+// Shapes of the wave-split kernel: X(16-row blocks per workgroup, n-tiles per
+// wave, waves side by side along N, activation slots in halves of a k-group,
+// weight slots in k-groups, us per launch, us per k-group).
+#define QUICK_WSPLIT_SHAPES(X) \
+    X(2, 1, 1, 4, 2, 2.5f, 0.113f) \
+    X(2, 2, 1, 4, 2, 4.0f, 0.129f) \
+    X(2, 3, 1, 4, 2, 4.5f, 0.160f) \
+    X(2, 4, 1, 4, 2, 5.5f, 0.186f) \
+    X(2, 3, 2, 4, 2, 3.0f, 0.323f) \
+    X(2, 4, 2, 4, 2, 4.0f, 0.400f) \
+    X(3, 2, 1, 2, 2, 4.0f, 0.155f) \
+    X(3, 3, 1, 2, 2, 4.5f, 0.183f) \
+    X(3, 4, 2, 4, 2, 8.0f, 0.399f) \
+    X(4, 1, 1, 2, 2, 2.5f, 0.179f) \
+    X(4, 2, 1, 2, 2, 3.5f, 0.205f) \
+    X(4, 3, 1, 2, 2, 4.5f, 0.226f) \
+    X(4, 4, 1, 2, 2, 5.5f, 0.272f) \
+    X(4, 2, 2, 4, 2, 4.5f, 0.306f) \
+    X(4, 3, 2, 4, 2, 6.0f, 0.389f) \
+    X(4, 2, 4, 4, 2, 4.5f, 0.493f) \
+    X(5, 2, 2, 2, 2, 5.0f, 0.373f) \
+    X(5, 4, 4, 4, 2, 11.5f, 1.007f) \
+    X(5, 4, 8, 4, 2, 15.0f, 1.916f) \
+    X(6, 3, 2, 2, 2, 7.5f, 0.535f) \
+    X(6, 2, 4, 4, 2, 6.5f, 0.666f) \
+    X(6, 4, 4, 4, 2, 12.5f, 1.110f) \
+    X(8, 2, 4, 4, 2, 8.5f, 0.764f) \
+    X(8, 3, 4, 4, 2, 12.5f, 1.041f) \
+    X(8, 2, 8, 4, 2, 11.0f, 1.335f) \
+    X(8, 3, 8, 4, 2, 18.0f, 1.871f) \
+    X(8, 4, 8, 4, 2, 22.5f, 2.400f)
+
+#if QUICK_WSPLIT
+// ---------------------------------------------------------------------------
+// Wave-split kernel (17 <= M <= 256).
+// ---------------------------------------------------------------------------
+constexpr int kWsWaves = 8;
+
+template <int MTT, int NP, int NW, int RH, int DW, bool GRP = false>
+__global__ void __launch_bounds__(64 * kWsWaves)
+wsplit_kernel(const uint16_t* x, const u4_t* pw, const uint16_t* ps, const uint32_t* pz, uint16_t* y, float* ws, int M,
+              int N, int K, int kgps, int n_mtiles, int n_cg, int S, GroupArgs ga, Epi epi)
+{
+    constexpr int WAVES = kWsWaves;
+    constexpr int KW = WAVES / NW;               // K ranges
+    constexpr int HALF = MTT * 2048;             // bytes of half a k-group (64 channels) of BM rows
+    constexpr int STAGE = KW * HALF;
+    constexpr int NX = (2 * MTT + NW - 1) / NW;   // copy instructions per wave and half
+    constexpr int PA = (NP + 1) / 2, PB = NP - PA;
+    static_assert(RH == 2 || (RH == 4 && DW % 2 == 0), "static slots over the unrolled k-groups");
+    static_assert(DW >= 2, "weights are requested at least one k-group ahead");
+    __shared__ __attribute__((aligned(1024))) uint8_t lds_s0[STAGE];
+    __shared__ __attribute__((aligned(1024))) uint8_t lds_s1[STAGE];
+    __shared__ __attribute__((aligned(1024))) uint8_t lds_s2[RH > 2 ? STAGE : 16];
+    __shared__ __attribute__((aligned(1024))) uint8_t lds_s3[RH > 2 ? STAGE : 16];
+    __shared__ int last_arrival;
+    auto stage_ptr = [&](int st) -> uint8_t* {
+        if constexpr (RH == 2) return st == 0 ? lds_s0 : lds_s1;
+        else return st == 0 ? lds_s0 : st == 1 ? lds_s1 : st == 2 ? lds_s2 : lds_s3;
+    };
+    const int KG = K >> 7;
+    const int NT = N >> 4;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int kw = wave / NW;        // K range of this wave
+    const int nw = wave - kw * NW;   // column group of this wave
+    const int c = lane & 15;
+    const int g = lane >> 4;
+
+    // ---- the workgroup's tile.  Consecutive tiles (M fastest, then N, then
+    // K slices; grouped: expert, N, the expert's M) run on one XCD and share
+    // weights in its L2.
+    int m0, mend = M, cg, s = 0, tin;
+    if constexpr (GRP) {
+        // per expert its routed rows [g_lo, g_hi) and the number of BM-row
+        // tiles of all experts before it, as in tiled_kernel
+        __shared__ int g_lo[kMaxExperts + 1], g_hi[kMaxExperts + 1], g_cum[kMaxExperts + 1];
+        if (wave == 0) {
+            int carry = 0;
+            for (int e0 = 0; e0 < ga.experts; e0 += 64) {
+                const int e = e0 + lane;
+                int lo = 0, hi = 0;
+                if (e < ga.experts) {
+                    lo = min(max(ga.offsets[e], 0), ga.routed);
+                    hi = min(max(ga.offsets[e + 1], lo), ga.routed);
+                }
+                int n = (hi - lo + MTT * 16 - 1) / (MTT * 16);
+#pragma unroll
+                for (int d = 1; d < 64; d <<= 1) {
+                    const int v = __shfl_up(n, d, 64);
+                    if (lane >= d) n += v;
+                }
+                if (e < ga.experts) {
+                    g_lo[e] = lo;
+                    g_hi[e] = hi;
+                    g_cum[e + 1] = carry + n;
+                }
+                carry += __shfl(n, 63, 64);
+            }
+            if (lane == 0) g_cum[0] = 0;
+        }
+        __syncthreads();
+        // the grid covers the host's upper bound; the tiles there are go
+        // evenly over the XCDs
+        const int tiles = (int)uniform(g_cum[ga.experts]) * n_cg;
+        const int per = (tiles + 7) >> 3;
+        tin = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+        if ((int)(blockIdx.x >> 3) >= per || tin >= tiles) return;
+        int lo = 0, hi = ga.experts;   // the last e with g_cum[e] * n_cg <= tin
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (g_cum[mid] * n_cg <= tin) lo = mid;
+            else hi = mid;
+        }
+        const int e = uniform(lo);
+        const int local = tin - (int)uniform(g_cum[e]) * n_cg;
+        const int tiles_e = (int)uniform(g_cum[e + 1] - g_cum[e]);
+        cg = local / tiles_e;
+        m0 = (int)uniform(g_lo[e]) + (local - cg * tiles_e) * (MTT * 16);
+        mend = uniform(g_hi[e]);
+        const size_t units = (size_t)(N >> 4) * (K >> 7);   // of one expert
+        pw += (size_t)e * units * 64;
+        ps += (size_t)e * units * 16;
+        pz += (size_t)e * units * 2;
+        if (epi.bias) epi.bias += (size_t)e * N;
+    } else {
+        const int t = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+        const int tiles = n_mtiles * n_cg;
+        if (t >= tiles * S) return;
+        s = t / tiles;
+        tin = t - s * tiles;
+        cg = tin / n_mtiles;
+        m0 = (tin - cg * n_mtiles) * (MTT * 16);
+    }
+    const int ntg = cg * (NW * NP);          // first n-tile of the workgroup
+    const int nt0 = ntg + nw * NP;           // ... of this wave
+    const int kb0 = s * kgps;
+    const int nks = min(KG, kb0 + kgps) - kb0;
+    const int kb = kb0 + nks * kw / KW;
+    const int nk = kb0 + nks * (kw + 1) / KW - kb;
+
+    const uint32_t wbytes = (uint32_t)((size_t)K * N / 2), xbytes = (uint32_t)((size_t)M * K * 2);
+    uint32_t ubase[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) ubase[p] = (uint32_t)min(nt0 + p, NT - 1) * KG;
+    const uint32_t vw = lane * 16;
+    const uint32_t vs = c * 2;
+    const uint32_t vz = (c >> 3) * 4;
+    // copy instruction i of a half k-group: 8 rows x 128 bytes (whole lines),
+    // lane L fills row L / 8, position L % 8 with channel chunk
+    // (L % 8) ^ (row / 2) of the half; this wave's are nw, nw + NW, .. (past
+    // the last one it repeats it)
+    auto copy_of = [&](int i) { return min(nw + i * NW, 2 * MTT - 1); };
+    uint32_t vx[NX];
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+        const int ii = copy_of(i);
+        int row = min(m0 + ii * 8 + (lane >> 3), mend - 1);
+        if constexpr (GRP) {
+            if (ga.rows) row = ga.rows[row];   // gather
+            row = min(max(row, 0), M - 1);
+        }
+        vx[i] = (uint32_t)row * (uint32_t)K * 2 + (((lane & 7) ^ (4 * (ii & 1) + (lane >> 4))) << 4);
+    }
+    // fragment of step j: row c of block mt, chunk 4 (j % 2) + g of the half,
+    // at position chunk ^ (c / 2)
+    uint32_t vf[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) vf[i] = (uint32_t)(kw * HALF + c * 128 + (((4 * i + g) ^ (c >> 1)) << 4));
+
+    f4_t acc[NP][MTT];
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+        for (int mt = 0; mt < MTT; ++mt) acc[p][mt] = f4_t{0.f, 0.f, 0.f, 0.f};
+
+    u4_t wr[DW][NP];
+    uint32_t sr[DW][NP], zr[DW][NP];
+    auto load_w = [&](int slot, int i) __attribute__((always_inline)) {
+        // past the range: descriptors of size 0, so that the loads count but
+        // move nothing
+        const uint32_t n = i < nk ? wbytes : 0;
+        const rsrc_t rw = make_rsrc(pw, n), rs = make_rsrc(ps, n / 32), rz = make_rsrc(pz, n / 128);
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const uint32_t u = uniform(ubase[p] + kb + i);
+            wr[slot][p] = ld128(rw, vw, u * 1024u);
+            sr[slot][p] = ld16(rs, vs, u * 32u);
+            zr[slot][p] = ld32(rz, vz, u * 8u);
+        }
+        asm volatile("" ::: "memory");
+        sched_fence();
+    };
+    auto issue_x = [&](int slot, int half) __attribute__((always_inline)) {
+        const rsrc_t rx = make_rsrc(x, half < 2 * nk ? xbytes : 0);
+        const uint32_t soff = uniform((uint32_t)(2 * kb + half) * 128u);
+#pragma unroll
+        for (int i = 0; i < NX; ++i) dma16(rx, stage_ptr(slot) + kw * HALF + copy_of(i) * 1024, vx[i], soff);
+    };
+    h8_t fa[PB ? 1 : 2][NP];   // weights of the step (one n-tile: double-buffered)
+    h8_t fb[MTT];              // activations of the step
+    Deq dq[NP];
+    auto make_d = [&](int slot) __attribute__((always_inline)) {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) dq[p] = make_deq(sr[slot][p], (zr[slot][p] >> (4 * (c & 7))) & 15u);
+    };
+    auto read_b = [&](int slot, int j, int mt) -> h8_t {
+        return bits_as<h8_t>(*reinterpret_cast<const u4_t*>(stage_ptr(slot) + vf[j & 1] + mt * 2048));
+    };
+    // One k-group (the i-th of this wave) in weight slot U.  It also reads
+    // and dequantizes the first step of the next one, past the last k-group
+    // whatever the buffers hold.
+    auto body = [&](auto uc, int i) __attribute__((always_inline)) {
+        constexpr int U = decltype(uc)::value;
+        load_w((U + DW - 1) % DW, i + DW - 1);
+        sched_fence();
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int cu = PB ? 0 : j & 1, nx = PB ? 0 : cu ^ 1;
+            // first n-tiles; the others' weights of this step meanwhile
+            if constexpr (PB > 0) {
+#pragma unroll
+                for (int p = PA; p < NP; ++p) fa[0][p] = dequant8(wr[U][p][j], dq[p]);
+#pragma unroll
+                for (int mt = 0; mt < MTT; ++mt)
+#pragma unroll
+                    for (int p = 0; p < PA; ++p) acc[p][mt] = mfma16(fa[0][p], fb[mt], acc[p][mt]);
+#pragma unroll
+                for (int mt = 0; mt < MTT; ++mt) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, PA, 0);                          // matrix
+                    __builtin_amdgcn_sched_group_barrier(0x002, (13 * PB + MTT - 1) / MTT, 0);   // VALU
+                }
+                sched_fence();
+            }
+            if (j % 2 == 1) {
+                // Step j+1 opens the next half.  Its copy has landed once at
+                // most the later requests of this wave are outstanding
+                // (copies are requested at odd steps, weights before step
+                // 0).  Private copies: the slot of this half is free once
+                // its fragments have been read.  Shared ones: behind the
+                // barrier the other waves' copies have landed too, and no
+                // wave still reads this half.
+                constexpr auto allowed = [](int jj) constexpr {
+                    int n = 0;
+                    const int t0 = jj - 2 * (RH - 1);   // step at which the copy for step jj+1 was requested
+                    for (int q = t0 + 1; q <= jj; ++q) {
+                        if (q % 4 == 0) n += 3 * NP;
+                        if (((q % 2) + 2) % 2 == 1 && (NW == 1 || q < jj)) n += NX;
+                    }
+                    return n;
+                };
+                auto refill = [&]() __attribute__((always_inline)) {
+                    issue_x((2 * U + (j >> 1)) % RH, 2 * i + (j >> 1) + RH);
+                    sched_fence();
+                };
+                wait_lds();
+                if constexpr (NW == 1) refill();
+                if (j == 1) wait_vm<allowed(1)>();
+                else wait_vm<allowed(3)>();
+                if constexpr (NW > 1) barrier();
+                asm volatile("" ::: "memory");
+                if constexpr (NW > 1) refill();
+            }
+            if (j == 3) make_d((U + 1) % DW);
+            // the other n-tiles; the next step's activations and first
+            // n-tiles' weights meanwhile
+            constexpr int PF = PB ? PB : NP, P0 = PB ? PA : 0;
+#pragma unroll
+            for (int p = 0; p < PA; ++p)
+                fa[nx][p] = dequant8(j < 3 ? wr[U][p][(j + 1) & 3] : wr[(U + 1) % DW][p][0], dq[p]);
+#pragma unroll
+            for (int mt = 0; mt < MTT; ++mt) {
+#pragma unroll
+                for (int p = P0; p < NP; ++p) acc[p][mt] = mfma16(fa[cu][p], fb[mt], acc[p][mt]);
+                fb[mt] = read_b((2 * U + ((j + 1) >> 1)) % RH, j + 1, mt);
+            }
+#pragma unroll
+            for (int mt = 0; mt < MTT; ++mt) {
+                __builtin_amdgcn_sched_group_barrier(0x008, PF, 0);                          // matrix
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                           // LDS read
+                __builtin_amdgcn_sched_group_barrier(0x002, (13 * PA + MTT - 1) / MTT, 0);   // VALU
+            }
+            sched_fence();
+        }
+    };
+
+    // the requests of the steps before the first, in the order of the
+    // steady state
+#pragma unroll
+    for (int q = -2 * RH - 4 * DW; q < 0; ++q) {
+        const int i = q / 4 + DW - 1;
+        if (q % 4 == 0 && i >= 0) load_w(i, i);
+        const int h = (q - 1) / 2 + RH;
+        if (q & 1 && h >= 0) issue_x(h, h);
+        sched_fence();
+    }
+    // the first half has landed
+    constexpr auto after0 = []() constexpr {
+        int n = 0;
+        for (int q = 1 - 2 * RH + 1; q < 0; ++q) {
+            if (q % 4 == 0 && q / 4 + DW - 1 >= 0) n += 3 * NP;
+            if (q & 1) n += NX;
+        }
+        return n;
+    };
+    wait_vm<after0()>();
+    if constexpr (NW > 1) barrier();
+    asm volatile("" ::: "memory");
+    make_d(0);
+#pragma unroll
+    for (int mt = 0; mt < MTT; ++mt) fb[mt] = read_b(0, 0, mt);
+#pragma unroll
+    for (int p = 0; p < PA; ++p) fa[0][p] = dequant8(wr[0][p][0], dq[p]);
+    sched_fence();
+    for (int i = 0; i < nk;) {
+        [&]<int... U>(std::integer_sequence<int, U...>) {
+            (void)((body(std::integral_constant<int, U>{}, i), ++i < nk) && ...);
+        }(std::make_integer_sequence<int, DW>{});
+    }
+    // waves that share copies meet at the same barriers: the shorter K
+    // ranges at those of one more k-group
+    if (NW > 1 && nk < (nks + KW - 1) / KW) {
+        barrier();
+        barrier();
+    }
+    // requests past the end (of size 0) still count and may write
+    wait_all();
+
+    // ---- sum of the K ranges' partial tiles, in order of K.  A block is the
+    // 16 x 16 part of GP neighbouring n-tiles (a gate tile and its up tile
+    // where the wave's n-tiles pair up) that one wave finishes.
+    constexpr int GP = NP % 2 == 0 ? 2 : 1;
+    constexpr int PFIT = 2 * RH / NW > GP ? 2 * RH / NW / GP * GP : GP;   // n-tiles of a wave the LDS holds
+    constexpr int PC = NP < PFIT ? NP : PFIT;                            // ... exchanged at once
+    static_assert(KW == 1 || PC * WAVES * MTT * 1024 <= RH * STAGE, "exchange fits");
+    constexpr int CH = KW == 1 ? 1 : (NP + PC - 1) / PC;
+    constexpr int NI = PC / GP * NW * MTT;                                   // blocks per exchange
+    constexpr int QI = KW == 1 ? NP / GP * MTT : (NI + WAVES - 1) / WAVES;   // ... per wave
+    f4_t tot[CH][QI][GP];
+    if constexpr (KW == 1) {
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int mt = 0; mt < MTT; ++mt) tot[0][p / GP * MTT + mt][p % GP] = acc[p][mt];
+    } else {
+        // part (p, column wave, mt) of K range k at 1 KiB slot
+        // (p * KW + k) * NW * MTT + column wave * MTT + mt
+        constexpr int PER = STAGE / 1024;   // slots per LDS object
+        auto slot_ptr = [&](int o) -> uint8_t* { return stage_ptr(o / PER) + (o % PER) * 1024 + lane * 16; };
+#pragma unroll
+        for (int ch = 0; ch < CH; ++ch) {
+            __syncthreads();
+#pragma unroll
+            for (int p = 0; p < PC; ++p)
+                if (ch * PC + p < NP) {
+#pragma unroll
+                    for (int mt = 0; mt < MTT; ++mt)
+                        *reinterpret_cast<f4_t*>(slot_ptr((p * KW + kw) * NW * MTT + nw * MTT + mt)) =
+                            acc[(ch * PC + p) % NP][mt];
+                }
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < QI; ++q) {
+                const int it = q * WAVES + wave;
+                const int pp = it / (NW * MTT);
+                if (it < NI && ch * PC + pp * GP < NP) {
+#pragma unroll
+                    for (int h = 0; h < GP; ++h) {
+                        f4_t sum;
+#pragma unroll
+                        for (int k = 0; k < KW; ++k) {
+                            const f4_t v = *reinterpret_cast<const f4_t*>(
+                                slot_ptr(((pp * GP + h) * KW + k) * NW * MTT + (it - pp * NW * MTT)));
+                            if (k == 0) sum = v;
+                            else sum += v;
+                        }
+                        tot[ch][q][h] = sum;
+                    }
+                }
+            }
+        }
+    }
+    // f(values of the block's GP n-tiles, row, first n-tile)
+    auto each = [&](auto&& f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int ch = 0; ch < CH; ++ch)
+#pragma unroll
+            for (int q = 0; q < QI; ++q) {
+                int nt, mt;
+                bool in = true;
+                if constexpr (KW == 1) {
+                    nt = nt0 + q / MTT * GP;
+                    mt = q % MTT;
+                } else {
+                    const int it = q * WAVES + wave;
+                    const int pp = it / (NW * MTT), r = it - pp * NW * MTT;
+                    const int w = r / MTT;
+                    mt = r - w * MTT;
+                    nt = ntg + w * NP + ch * PC + pp * GP;
+                    in = it < NI && ch * PC + pp * GP < NP;
+                }
+                const int m = m0 + mt * 16 + c;
+                if (in && m < mend) f(tot[ch][q], m, nt);
+            }
+    };
+    if (!GRP && S > 1) {
+        // partial outputs [S][M][N].  From kWsReduceSplit slices on the
+        // reduction pass adds them, spread over the whole chip; the few of a
+        // smaller split are added by the last slice of the tile to arrive,
+        // in slice order (device-coherent stores and loads).
+        const rsrc_t rp = make_rsrc(ws + kSkCounterBytes / sizeof(float), (uint32_t)((size_t)S * M * N * 4));
+        const uint32_t plane = (uint32_t)M * (uint32_t)N * 4u;
+        const bool pass = S >= kWsReduceSplit;
+        each([&](f4_t (&v)[GP], int m, int nt) {
+#pragma unroll
+            for (int h = 0; h < GP; ++h) {
+                if (nt + h >= NT) continue;
+                const uint32_t off = (uint32_t)(m * N + (nt + h) * 16 + 4 * g) * 4u;
+                if (pass)
+                    __builtin_amdgcn_raw_buffer_store_b128(bits_as<u4_t>(v[h]), rp, off, uniform((uint32_t)s * plane), 0);
+                else
+                    __builtin_amdgcn_raw_buffer_store_b128(bits_as<u4_t>(v[h]), rp, off, uniform((uint32_t)s * plane),
+                                                           kCoherentAux);
+            }
+        });
+        if (pass) return;
+        unsigned* counters = reinterpret_cast<unsigned*>(ws);
+        wait_all();
+        __syncthreads();
+        if (threadIdx.x == 0)
+            last_arrival = __hip_atomic_fetch_add(&counters[tin], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                           (unsigned)(S - 1);
+        __syncthreads();
+        if (!last_arrival) return;
+        each([&](f4_t (&v)[GP], int m, int nt) {
+#pragma unroll
+            for (int h = 0; h < GP; ++h) {
+                if (nt + h >= NT) continue;
+                f4_t sum = f4_t{0.f, 0.f, 0.f, 0.f};
+                for (int ss = 0; ss < S; ++ss) {
+                    const f4_t o = ss == s ? v[h]
+                                           : bits_as<f4_t>(__builtin_amdgcn_raw_buffer_load_b128(
+                                                 rp, (uint32_t)(m * N + (nt + h) * 16 + 4 * g) * 4u,
+                                                 uniform((uint32_t)ss * plane), kCoherentAux));
+                    sum = ss == 0 ? o : sum + o;
+                }
+                v[h] = sum;
+            }
+        });
+        if (threadIdx.x == 0) __hip_atomic_store(&counters[tin], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (GP == 2 && epi.act) {
+        each([&](f4_t (&v)[GP], int m, int nt) {
+            if (nt < NT) store_gated(y, epi, m, N, nt * 16 + 4 * g, v[0], v[GP - 1]);
+        });
+        return;
+    }
+    each([&](f4_t (&v)[GP], int m, int nt) {
+#pragma unroll
+        for (int h = 0; h < GP; ++h)
+            if (nt + h < NT) store_out(y, epi, m, N, (nt + h) * 16 + 4 * g, v[h]);
+    });
+}
+#endif  // QUICK_WSPLIT
+
 // Sum of S fp32 partial outputs [S][rows][N] in split order, then the
 // epilogue and one rounding to f16.  One thread per 4 output columns.
 __global__ void __launch_bounds__(256)
@@ -2085,6 +2555,18 @@ void finish_plan(int64_t M, int64_t N, int64_t K, Plan* pl)
     }
 }
 
+bool is_auto_config(const quick_config_t& c) { return !c.variant && !c.split_k && !c.tile_m && !c.tile_n; }
+
+// Whether the launch is left to the rules (no configuration, none recorded
+// for the shape, or one with every field 0): only then may it run in the
+// wave-split form, which no explicit configuration names.
+bool is_automatic(int64_t M, int64_t N, int64_t K, const quick_config_t* cfg)
+{
+    if (cfg) return is_auto_config(*cfg);
+    quick_config_t tuned;
+    return !tuned_config(M, N, K, &tuned) || is_auto_config(tuned);
+}
+
 // Workspace layout: kSkCounterBytes of stream-K arrival counters (zero
 // between calls), then split-K partial outputs or stream-K partial tiles.
 size_t plan_workspace(int64_t M, int64_t N, const Plan& pl)
@@ -2386,6 +2868,49 @@ int launch_ablation(const uint16_t* x, const u4_t* pw, const uint16_t* ps, const
 
 #endif  // QUICK_TILED
 
+#if QUICK_WSPLIT
+template <int MTT, int NP, int NW, int RH, int DW>
+void launch_wsplit_t(const WsplitPlan& wp, const uint16_t* x, const u4_t* pw, const uint16_t* ps, const uint32_t* pz,
+                     uint16_t* y, float* ws, int M, int N, int K, hipStream_t st, const Epi& epi)
+{
+    const int nm = ceil_div(M, MTT * 16), ncg = ceil_div(N / 16, NP * NW);
+    const dim3 grid((unsigned)ceil_div((int64_t)nm * ncg * wp.split, 8) * 8);
+    hipLaunchKernelGGL((wsplit_kernel<MTT, NP, NW, RH, DW>), grid, dim3(64 * kWsWaves), 0, st, x, pw, ps, pz, y, ws, M,
+                       N, K, wp.kgps, nm, ncg, wp.split, GroupArgs{}, epi);
+}
+
+int launch_wsplit(const WsplitPlan& wp, const uint16_t* x, const u4_t* pw, const uint16_t* ps, const uint32_t* pz,
+                  uint16_t* y, float* ws, int M, int N, int K, hipStream_t st, const Epi& epi)
+{
+    bool known = false;
+#define QUICK_WS(MTT, NP, NW, RH, DW, F, S)                                                  \
+    if (!known && wp.mt == MTT && wp.np == NP && wp.nw == NW) {                              \
+        launch_wsplit_t<MTT, NP, NW, RH, DW>(wp, x, pw, ps, pz, y, ws, M, N, K, st, epi);    \
+        known = true;                                                                        \
+    }
+    QUICK_WSPLIT_SHAPES(QUICK_WS)
+#undef QUICK_WS
+    if (!known) return QUICK_ERR_INVALID_ARG;
+    if (wp.split >= kWsReduceSplit) {
+        const int64_t quads = (int64_t)M * (epi.act ? N / 2 : N) / 4;
+        hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, st,
+                           ws + kSkCounterBytes / sizeof(float), y, (int64_t)M, N, wp.split, epi);
+    }
+    return QUICK_OK;
+}
+#ifdef QUICK_DEV
+extern "C" int quick_dev_wsplit(const void* x, const void* packed, const void* scales, const void* zeros, void* y,
+                                int64_t M, int64_t N, int64_t K, void* ws, int mt, int np, int nw, int split, void* stream)
+{
+    const int kg = (int)(K / 128);
+    WsplitPlan wp{mt, np, nw, split, ceil_div(kg, split)};
+    wp.split = ceil_div(kg, wp.kgps);
+    return launch_wsplit(wp, (const uint16_t*)x, (const u4_t*)packed, (const uint16_t*)scales, (const uint32_t*)zeros,
+                         (uint16_t*)y, (float*)ws, (int)M, (int)N, (int)K, (hipStream_t)stream, Epi{nullptr, 0});
+}
+#endif
+#endif  // QUICK_WSPLIT
+
 }  // namespace quick
 
 #if QUICK_HOST
@@ -2396,6 +2921,64 @@ using quick::launch_kstream;
 using quick::launch_stream;
 using quick::launch_tiled;
 using quick::launch_tiled32;
+using quick::launch_wsplit;
+using quick::WsplitPlan;
+
+// Shape of the wave-split launch for a GEMM of M > 16 rows: the one whose
+// estimated time is least.  The estimate is
+//   fixed + rounds * k-groups * us per k-group + 0.9 * fixed per further round
+// with the two constants of each shape in QUICK_WSPLIT_SHAPES fitted to 5400
+// timings of the shapes over 100 random GEMMs (17 <= M <= 2048, N and K from
+// 1024, cold weights), a last round of r < 256 workgroups counted as
+// 0.9 + 0.1 r / 256 of a full one (256 compute units, one workgroup each),
+// and not under the time of reading the weights at 4.2 TB/s.  Splitting K
+// costs the traffic of its fp32 partial sums and, from kWsReduceSplit slices
+// on, a second launch.  On those GEMMs the choice is on average 0.9 % (at most
+// 9 %) slower than the best shape, and 1.29 times as fast (never slower) as
+// the tiled kernels on their own rules.  A split uses no more workspace than
+// `ws_bytes`, what the tiled plan needs.
+struct WsShape {
+    int mt, np, nw;
+    float fixed, per_kg;
+};
+constexpr WsShape kWsShapes[] = {
+#define QUICK_WS(MTT, NP, NW, RH, DW, F, S) WsShape{MTT, NP, NW, F, S},
+    QUICK_WSPLIT_SHAPES(QUICK_WS)
+#undef QUICK_WS
+};
+constexpr int kWsCus = 256;
+
+bool wsplit_plan(int64_t M, int64_t N, int64_t K, size_t ws_bytes, const Epi& epi, WsplitPlan* out)
+{
+    if (M <= 16) return false;
+    const int64_t KG = K / 128;
+    const double read_us = (double)K * N * 0.52 / 4.2e6 + 2.5;
+    double best = 0;
+    bool found = false;
+    for (const WsShape& w : kWsShapes) {
+        if (epi.act && w.np % 2) continue;   // a gate tile and its up tile in one wave
+        const int64_t tiles = ((M + 16 * w.mt - 1) / (16 * w.mt)) * ((N / 16 + w.np * w.nw - 1) / (w.np * w.nw));
+        for (int s = 1; s <= 8; s *= 2) {
+            const int64_t part = (int64_t)s * M * N * 4;
+            if (s > 1 && (KG / s < 4 || tiles * s > 2 * kWsCus || tiles > kSkMaxWorkgroups ||
+                          kSkCounterBytes + part > ws_bytes || part >= ((int64_t)1 << 32)))
+                break;
+            const int kgps = ceil_div(KG, s);
+            const int64_t wgs = tiles * s, full = wgs / kWsCus, rest = wgs % kWsCus;
+            const double rounds = (double)full + (rest ? 0.9 + 0.1 * (double)rest / kWsCus : 0.0);
+            double us = w.fixed + rounds * kgps * w.per_kg + 0.9 * w.fixed * (double)((wgs + kWsCus - 1) / kWsCus - 1);
+            if (s >= kWsReduceSplit) us += 4.5 + 0.25e-6 * (double)part;
+            else if (s > 1) us += 2.1 + 0.4e-6 * (double)part;
+            us = std::max(us, read_us);
+            if (!found || us < best) {
+                best = us;
+                found = true;
+                *out = WsplitPlan{w.mt, w.np, w.nw, ceil_div(KG, kgps), kgps};
+            }
+        }
+    }
+    return found;
+}
 
 bool grouped_tile_supported(int bm, int wn)
 {
@@ -2461,6 +3044,8 @@ int gemm_impl(const void* x, const void* packed, const void* scales, const void*
     finish_plan(M, N, K, &pl);
     hipStream_t hs = (hipStream_t)stream;
     const size_t need = plan_workspace(M, N, pl);
+    WsplitPlan wp;
+    const bool wave = is_automatic(M, N, K, cfg) && wsplit_plan(M, N, K, need, epi, &wp);
     void* ws = nullptr;
     if (need) {
         if (workspace) {
@@ -2478,7 +3063,9 @@ int gemm_impl(const void* x, const void* packed, const void* scales, const void*
     const uint32_t* pz = static_cast<const uint32_t*>(zeros);
     uint16_t* yy = static_cast<uint16_t*>(y);
     (void)hipGetLastError();  // clear a stale error so the check below is ours
-    if (pl.variant == kVariantStream)
+    if (wave)
+        st = launch_wsplit(wp, xx, pw, ps, pz, yy, static_cast<float*>(ws), (int)M, (int)N, (int)K, hs, epi);
+    else if (pl.variant == kVariantStream)
         st = launch_stream(pl, xx, pw, ps, pz, yy, (int)M, (int)N, (int)K, hs, epi);
     else if (pl.variant == kVariantKStream)
         st = launch_kstream(pl, xx, pw, ps, pz, yy, static_cast<float*>(ws), (int)M, (int)N, (int)K, hs, epi);
@@ -2593,16 +3180,16 @@ extern "C" int quick_select_config(int64_t M, int64_t N, int64_t K, quick_config
     Plan pl;
     if (make_plan(M, N, K, nullptr, &pl) != QUICK_OK) auto_plan(M, N, K, &pl);
     finish_plan(M, N, K, &pl);
-    cfg->variant = pl.variant;
-    cfg->split_k = pl.split;
-    cfg->tile_m = is_tiled(pl.variant) ? pl.bm : 0;
-    cfg->tile_n = pl.wn;
+    *cfg = quick_config_t{pl.variant, pl.split, is_tiled(pl.variant) ? pl.bm : 0, pl.wn};
+    quick_config_t tuned;
+    if (tuned_config(M, N, K, &tuned) && is_auto_config(tuned)) *cfg = tuned;   // tuned to the rules' choice
     return QUICK_OK;
 }
 
 namespace {
 
-// Configurations worth timing for a shape: the stream kernel (small M), the
+// Configurations worth timing for a shape: the automatic choice (whose
+// wave-split form no other configuration names), the stream kernel (small M), the
 // sliced stream kernel (M <= 16), the tiled tiles no taller than the next
 // power of two >= M (at least 16) with splits 1, 2, 4, 8 (each slice keeping
 // >= 2 k-groups), and stream-K.
@@ -2610,6 +3197,7 @@ std::vector<quick_config_t> tune_candidates(int64_t M, int64_t N, int64_t K)
 {
     std::vector<quick_config_t> c;
     const int64_t KG = K / 128;
+    c.push_back(quick_config_t{0, 0, 0, 0});   // the rules' own choice
     if (M <= 64)
         for (int w : {1, 2, 4, 8})
             for (int p : {1, 2}) c.push_back(quick_config_t{kVariantStream, w, 0, p});

@@ -52,6 +52,17 @@ struct Plan {
     int kgps;   // tiled split-K and sliced stream: k-groups per slice
 };
 
+// A launch of the wave-split kernel.
+struct WsplitPlan {
+    int mt;     // 16-row blocks per workgroup
+    int np;     // n-tiles per wave
+    int nw;     // waves side by side along N (8 / nw split K)
+    int split;  // K slices across workgroups
+    int kgps;   // k-groups per slice
+};
+int launch_wsplit(const WsplitPlan& wp, const uint16_t* x, const lu4_t* pw, const uint16_t* ps, const uint32_t* pz,
+                  uint16_t* y, float* ws, int M, int N, int K, hipStream_t st, const Epi& epi);
+
 // Stream-kernel part.
 int launch_stream(const Plan& pl, const uint16_t* x, const lu4_t* pw, const uint16_t* ps, const uint32_t* pz,
                   uint16_t* y, int M, int N, int K, hipStream_t st, const Epi& epi);
