@@ -24,7 +24,8 @@ UNITS = [("quick_pack.cpp", []),
          ("quick_gemm.hip", ["-DQUICK_PART=0"]),
          ("quick_gemm.hip", ["-DQUICK_PART=1"]),
          ("quick_gemm.hip", ["-DQUICK_PART=2"]),
-         ("quick_gemm.hip", ["-DQUICK_PART=3"])]
+         ("quick_gemm.hip", ["-DQUICK_PART=3"]),
+         ("quick_gemm.hip", ["-DQUICK_PART=4"])]
 
 
 def _msgs(r):

@@ -27,6 +27,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
@@ -52,11 +53,13 @@
 #define QUICK_STREAM 1
 #define QUICK_TILED 1
 #define QUICK_WSPLIT 1
+#define QUICK_WSPLIT_GRP 1
 #else
 #define QUICK_HOST (QUICK_PART == 0)
 #define QUICK_STREAM (QUICK_PART == 1)
 #define QUICK_TILED (QUICK_PART == 2)
 #define QUICK_WSPLIT (QUICK_PART == 3)
+#define QUICK_WSPLIT_GRP (QUICK_PART == 4)
 #endif
 
 namespace {
@@ -1715,35 +1718,54 @@ tiled32_kernel(const uint16_t* __restrict__ x, const u4_t* __restrict__ pw,
 // wave, waves side by side along N, activation slots in halves of a k-group,
 // weight slots in k-groups, us per launch, us per k-group).
 #define QUICK_WSPLIT_SHAPES(X) \
-    X(2, 1, 1, 4, 2, 2.5f, 0.113f) \
-    X(2, 2, 1, 4, 2, 4.0f, 0.129f) \
-    X(2, 3, 1, 4, 2, 4.5f, 0.160f) \
-    X(2, 4, 1, 4, 2, 5.5f, 0.186f) \
-    X(2, 3, 2, 4, 2, 3.0f, 0.323f) \
-    X(2, 4, 2, 4, 2, 4.0f, 0.400f) \
-    X(3, 2, 1, 2, 2, 4.0f, 0.155f) \
-    X(3, 3, 1, 2, 2, 4.5f, 0.183f) \
-    X(3, 4, 2, 4, 2, 8.0f, 0.399f) \
-    X(4, 1, 1, 2, 2, 2.5f, 0.179f) \
-    X(4, 2, 1, 2, 2, 3.5f, 0.205f) \
-    X(4, 3, 1, 2, 2, 4.5f, 0.226f) \
-    X(4, 4, 1, 2, 2, 5.5f, 0.272f) \
-    X(4, 2, 2, 4, 2, 4.5f, 0.306f) \
-    X(4, 3, 2, 4, 2, 6.0f, 0.389f) \
-    X(4, 2, 4, 4, 2, 4.5f, 0.493f) \
-    X(5, 2, 2, 2, 2, 5.0f, 0.373f) \
-    X(5, 4, 4, 4, 2, 11.5f, 1.007f) \
-    X(5, 4, 8, 4, 2, 15.0f, 1.916f) \
-    X(6, 3, 2, 2, 2, 7.5f, 0.535f) \
-    X(6, 2, 4, 4, 2, 6.5f, 0.666f) \
-    X(6, 4, 4, 4, 2, 12.5f, 1.110f) \
-    X(8, 2, 4, 4, 2, 8.5f, 0.764f) \
-    X(8, 3, 4, 4, 2, 12.5f, 1.041f) \
-    X(8, 2, 8, 4, 2, 11.0f, 1.335f) \
-    X(8, 3, 8, 4, 2, 18.0f, 1.871f) \
-    X(8, 4, 8, 4, 2, 22.5f, 2.400f)
+    X(1, 2, 1, 4, 4, 2.5f, 0.118f) \
+    X(1, 3, 1, 4, 2, 2.0f, 0.169f) \
+    X(1, 4, 1, 4, 2, 2.5f, 0.208f) \
+    X(2, 1, 1, 4, 2, 2.5f, 0.127f) \
+    X(2, 2, 1, 4, 2, 3.0f, 0.161f) \
+    X(2, 3, 1, 4, 2, 3.5f, 0.198f) \
+    X(2, 4, 2, 4, 2, 3.0f, 0.484f) \
+    X(3, 2, 1, 2, 2, 3.0f, 0.189f) \
+    X(3, 3, 2, 4, 2, 4.0f, 0.397f) \
+    X(3, 4, 2, 4, 2, 4.5f, 0.529f) \
+    X(4, 1, 1, 2, 2, 2.5f, 0.183f) \
+    X(4, 2, 1, 2, 2, 3.0f, 0.219f) \
+    X(4, 3, 1, 2, 2, 3.5f, 0.252f) \
+    X(4, 4, 1, 2, 2, 4.5f, 0.292f) \
+    X(4, 2, 2, 4, 2, 3.5f, 0.328f) \
+    X(4, 3, 2, 4, 2, 4.5f, 0.430f) \
+    X(4, 3, 4, 4, 2, 4.0f, 0.743f) \
+    X(5, 2, 2, 2, 2, 3.5f, 0.433f) \
+    X(5, 3, 2, 2, 2, 5.0f, 0.519f) \
+    X(5, 4, 4, 4, 2, 7.0f, 1.165f) \
+    X(5, 4, 8, 4, 2, 5.5f, 2.303f) \
+    X(6, 2, 4, 4, 2, 4.5f, 0.723f) \
+    X(6, 3, 2, 2, 2, 5.5f, 0.603f) \
+    X(6, 3, 4, 4, 2, 6.5f, 1.018f) \
+    X(6, 4, 4, 4, 2, 8.0f, 1.272f) \
+    X(6, 4, 8, 4, 2, 7.0f, 2.481f) \
+    X(8, 1, 4, 4, 2, 3.5f, 0.560f) \
+    X(8, 2, 4, 4, 2, 5.5f, 0.864f) \
+    X(8, 3, 4, 4, 2, 7.5f, 1.213f) \
+    X(8, 2, 8, 4, 2, 5.0f, 1.560f) \
+    X(8, 3, 8, 4, 2, 6.5f, 2.301f) \
+    X(8, 4, 8, 4, 2, 8.5f, 2.973f)
+// ... of its grouped form (even n-tiles per wave: a gate tile with its up tile).
+#define QUICK_WSPLIT_GRP_SHAPES(X) \
+    X(1, 2, 1, 4, 4, 2.5f, 0.118f) \
+    X(1, 4, 1, 4, 2, 2.5f, 0.208f) \
+    X(2, 4, 2, 4, 2, 3.0f, 0.484f) \
+    X(3, 4, 2, 4, 2, 4.5f, 0.529f) \
+    X(4, 2, 2, 4, 2, 3.5f, 0.328f) \
+    X(4, 4, 4, 4, 2, 5.5f, 0.990f) \
+    X(5, 4, 4, 4, 2, 7.0f, 1.165f) \
+    X(5, 4, 8, 4, 2, 5.5f, 2.303f) \
+    X(6, 4, 4, 4, 2, 8.0f, 1.272f) \
+    X(8, 2, 4, 4, 2, 5.5f, 0.864f) \
+    X(8, 2, 8, 4, 2, 5.0f, 1.560f) \
+    X(8, 4, 8, 4, 2, 8.5f, 2.973f)
 
-#if QUICK_WSPLIT
+#if QUICK_WSPLIT || QUICK_WSPLIT_GRP
 // ---------------------------------------------------------------------------
 // Wave-split kernel (17 <= M <= 256).
 // ---------------------------------------------------------------------------
@@ -2174,7 +2196,7 @@ wsplit_kernel(const uint16_t* x, const u4_t* pw, const uint16_t* ps, const uint3
             if (nt + h < NT) store_out(y, epi, m, N, (nt + h) * 16 + 4 * g, v[h]);
     });
 }
-#endif  // QUICK_WSPLIT
+#endif  // QUICK_WSPLIT || QUICK_WSPLIT_GRP
 
 // Sum of S fp32 partial outputs [S][rows][N] in split order, then the
 // epilogue and one rounding to f16.  One thread per 4 output columns.
@@ -2911,6 +2933,34 @@ extern "C" int quick_dev_wsplit(const void* x, const void* packed, const void* s
 #endif
 #endif  // QUICK_WSPLIT
 
+#if QUICK_WSPLIT_GRP
+template <int MTT, int NP, int NW, int RH, int DW>
+void launch_wsplit_grp_t(const uint16_t* x, const u4_t* pw, const uint16_t* ps, const uint32_t* pz, uint16_t* y, int M,
+                         int N, int K, hipStream_t st, const GroupArgs& ga, const Epi& epi)
+{
+    // the most m-tiles the experts' rows can make; the kernel counts them
+    const int64_t nm = ((int64_t)ga.routed + (int64_t)ga.experts * (MTT * 16 - 1)) / (MTT * 16);
+    const int ncg = ceil_div(N / 16, NP * NW);
+    const dim3 grid((unsigned)ceil_div(nm * ncg, 8) * 8);
+    hipLaunchKernelGGL((wsplit_kernel<MTT, NP, NW, RH, DW, true>), grid, dim3(64 * kWsWaves), 0, st, x, pw, ps, pz, y,
+                       (float*)nullptr, M, N, K, K / 128, 0, ncg, 1, ga, epi);
+}
+
+int launch_wsplit_grouped(const WsplitPlan& wp, const uint16_t* x, const u4_t* pw, const uint16_t* ps,
+                          const uint32_t* pz, uint16_t* y, int M, int N, int K, hipStream_t st, const GroupArgs& ga,
+                          const Epi& epi)
+{
+#define QUICK_WS(MTT, NP, NW, RH, DW, F, S)                                                 \
+    if (wp.mt == MTT && wp.np == NP && wp.nw == NW) {                                       \
+        launch_wsplit_grp_t<MTT, NP, NW, RH, DW>(x, pw, ps, pz, y, M, N, K, st, ga, epi);   \
+        return QUICK_OK;                                                                    \
+    }
+    QUICK_WSPLIT_GRP_SHAPES(QUICK_WS)
+#undef QUICK_WS
+    return QUICK_ERR_INVALID_ARG;
+}
+#endif  // QUICK_WSPLIT_GRP
+
 }  // namespace quick
 
 #if QUICK_HOST
@@ -2922,21 +2972,22 @@ using quick::launch_stream;
 using quick::launch_tiled;
 using quick::launch_tiled32;
 using quick::launch_wsplit;
+using quick::launch_wsplit_grouped;
 using quick::WsplitPlan;
 
-// Shape of the wave-split launch for a GEMM of M > 16 rows: the one whose
-// estimated time is least.  The estimate is
+// Shape of a wave-split launch: the one whose estimated time is least.  The
+// estimate is
 //   fixed + rounds * k-groups * us per k-group + 0.9 * fixed per further round
-// with the two constants of each shape in QUICK_WSPLIT_SHAPES fitted to 5400
-// timings of the shapes over 100 random GEMMs (17 <= M <= 2048, N and K from
-// 1024, cold weights), a last round of r < 256 workgroups counted as
-// 0.9 + 0.1 r / 256 of a full one (256 compute units, one workgroup each),
-// and not under the time of reading the weights at 4.2 TB/s.  Splitting K
-// costs the traffic of its fp32 partial sums and, from kWsReduceSplit slices
-// on, a second launch.  On those GEMMs the choice is on average 0.9 % (at most
-// 9 %) slower than the best shape, and 1.29 times as fast (never slower) as
-// the tiled kernels on their own rules.  A split uses no more workspace than
-// `ws_bytes`, what the tiled plan needs.
+// with the two constants of each shape in QUICK_WSPLIT_SHAPES fitted to 5600
+// timings of the shapes over 115 random GEMMs (17 <= M <= 2048, N and K from
+// 1024, back to back so that the chip runs at its sustained clock), a last
+// round of r < 256 workgroups counted as 0.8 + 0.2 r / 256 of a full one (256
+// compute units, one workgroup each), and not under the time of reading the
+// weights at 4.2 TB/s.  Splitting K costs the traffic of its fp32 partial sums
+// and, from kWsReduceSplit slices on, a second launch.  On those GEMMs the
+// choice is on average 1 % (at most 18 %) slower than the best shape, and 1.25
+// times as fast as the tiled kernels on their own rules (1 % slower at worst).
+// A split uses no more workspace than `ws_bytes`, what the tiled plan needs.
 struct WsShape {
     int mt, np, nw;
     float fixed, per_kg;
@@ -2948,15 +2999,44 @@ constexpr WsShape kWsShapes[] = {
 };
 constexpr int kWsCus = 256;
 
-bool wsplit_plan(int64_t M, int64_t N, int64_t K, size_t ws_bytes, const Epi& epi, WsplitPlan* out)
+// Estimated time of `tiles` workgroups of shape w over kg k-groups each.
+double wsplit_us(const WsShape& w, int64_t tiles, int64_t kg)
 {
-    if (M <= 16) return false;
+    const int64_t full = tiles / kWsCus, rest = tiles % kWsCus;
+    const double rounds = (double)full + (rest ? 0.8 + 0.2 * (double)rest / kWsCus : 0.0);
+    return w.fixed + rounds * (double)kg * w.per_kg + 0.9 * w.fixed * (double)((tiles + kWsCus - 1) / kWsCus - 1);
+}
+
+// M <= 16: whether the wave-split form (one 16-row block) is the faster one.
+// The stream kernel stages all of x in every workgroup: it wins while its
+// workgroups still run in one round (7B o-proj at M = 16: 5.7 against 7.2
+// us), and loses once few fit a compute unit (13B o-proj at M = 16, x past the
+// LDS: 13.1 against 8.4 us; 11008 x 9744 at M = 3, one workgroup per compute
+// unit in three rounds: 18.6 against 16.5 us).  The sliced stream kernel wins
+// while its workgroups are a single round (12288 x 4096 at M = 10: 9.9
+// against 10.0 us; 15360 x 5120 at M = 16, 360 workgroups: 15.0 against 12.4
+// us); the 16-row tiles never do.
+bool wsplit_small_m(int64_t M, int64_t N, int64_t K, const Plan& pl)
+{
+    if (pl.variant == kVariantKStream) return (int64_t)ks_groups(N, pl.wn) * pl.split > kWsCus;
+    if (pl.variant != kVariantStream) return true;
+    const size_t xb = (size_t)pl.split * stream_slice_bytes((int)M, (int)(K / 128), pl.split);
+    if (xb > kStreamLdsX) return true;
+    const size_t lds = xb + (pl.split > 1 ? (size_t)pl.split * pl.wn * 1024 : 0);
+    const int64_t per_cu = (int64_t)((160 * 1024) / std::max<size_t>(lds, 1));
+    return per_cu <= 2 && (N / 16 + pl.wn - 1) / pl.wn > kWsCus * per_cu;
+}
+
+bool wsplit_plan(int64_t M, int64_t N, int64_t K, const Plan& pl, size_t ws_bytes, const Epi& epi, WsplitPlan* out)
+{
+    if (M <= 16 && !wsplit_small_m(M, N, K, pl)) return false;
     const int64_t KG = K / 128;
     const double read_us = (double)K * N * 0.52 / 4.2e6 + 2.5;
     double best = 0;
     bool found = false;
     for (const WsShape& w : kWsShapes) {
         if (epi.act && w.np % 2) continue;   // a gate tile and its up tile in one wave
+        if ((M <= 16) != (w.mt == 1)) continue;
         const int64_t tiles = ((M + 16 * w.mt - 1) / (16 * w.mt)) * ((N / 16 + w.np * w.nw - 1) / (w.np * w.nw));
         for (int s = 1; s <= 8; s *= 2) {
             const int64_t part = (int64_t)s * M * N * 4;
@@ -2964,9 +3044,7 @@ bool wsplit_plan(int64_t M, int64_t N, int64_t K, size_t ws_bytes, const Epi& ep
                           kSkCounterBytes + part > ws_bytes || part >= ((int64_t)1 << 32)))
                 break;
             const int kgps = ceil_div(KG, s);
-            const int64_t wgs = tiles * s, full = wgs / kWsCus, rest = wgs % kWsCus;
-            const double rounds = (double)full + (rest ? 0.9 + 0.1 * (double)rest / kWsCus : 0.0);
-            double us = w.fixed + rounds * kgps * w.per_kg + 0.9 * w.fixed * (double)((wgs + kWsCus - 1) / kWsCus - 1);
+            double us = wsplit_us(w, tiles * s, kgps);
             if (s >= kWsReduceSplit) us += 4.5 + 0.25e-6 * (double)part;
             else if (s > 1) us += 2.1 + 0.4e-6 * (double)part;
             us = std::max(us, read_us);
@@ -2978,6 +3056,37 @@ bool wsplit_plan(int64_t M, int64_t N, int64_t K, size_t ws_bytes, const Epi& ep
         }
     }
     return found;
+}
+
+// The same for R routed rows over E experts, whose counts only the device
+// knows: the m-tiles are those of counts spread about the mean as under
+// uniform routing (standard deviation sqrt(mean)).
+constexpr WsShape kWsGrpShapes[] = {
+#define QUICK_WS(MTT, NP, NW, RH, DW, F, S) WsShape{MTT, NP, NW, F, S},
+    QUICK_WSPLIT_GRP_SHAPES(QUICK_WS)
+#undef QUICK_WS
+};
+
+WsplitPlan wsplit_grouped_plan(int64_t R, int64_t E, int64_t N, int64_t K)
+{
+    const double mean = (double)R / (double)E, dev = std::sqrt(mean);
+    static const double at[4] = {-1.5, -0.5, 0.5, 1.5}, weight[4] = {0.13, 0.37, 0.37, 0.13};
+    double best = 0;
+    WsplitPlan out{0, 0, 0, 1, (int)(K / 128)};
+    for (const WsShape& w : kWsGrpShapes) {
+        double per = 0;
+        for (int i = 0; i < 4; ++i) per += weight[i] * std::ceil(std::max(1.0, mean + at[i] * dev) / (16.0 * w.mt));
+        const int64_t nm = (int64_t)std::ceil(std::min(per, mean) * (double)E);
+        const int64_t tiles = nm * ((N / 16 + w.np * w.nw - 1) / (w.np * w.nw));
+        const double us = wsplit_us(w, tiles, K / 128);
+        if (!out.mt || us < best) {
+            best = us;
+            out.mt = w.mt;
+            out.np = w.np;
+            out.nw = w.nw;
+        }
+    }
+    return out;
 }
 
 bool grouped_tile_supported(int bm, int wn)
@@ -3045,7 +3154,7 @@ int gemm_impl(const void* x, const void* packed, const void* scales, const void*
     hipStream_t hs = (hipStream_t)stream;
     const size_t need = plan_workspace(M, N, pl);
     WsplitPlan wp;
-    const bool wave = is_automatic(M, N, K, cfg) && wsplit_plan(M, N, K, need, epi, &wp);
+    const bool wave = is_automatic(M, N, K, cfg) && wsplit_plan(M, N, K, pl, need, epi, &wp);
     void* ws = nullptr;
     if (need) {
         if (workspace) {
@@ -3601,6 +3710,16 @@ int grouped_impl(const void* x, const int32_t* rows, const int32_t* offsets, con
         }
     }
     (void)hipGetLastError();
+    const bool automatic = !cfg || is_auto_config(*cfg);
+    if (automatic) {
+        const GroupArgs ga{rows, offsets, (int)E, (int)R, 0, 0, 0};
+        st = launch_wsplit_grouped(wsplit_grouped_plan(R, E, N, K), static_cast<const uint16_t*>(x),
+                                   static_cast<const u4_t*>(packed), static_cast<const uint16_t*>(scales),
+                                   static_cast<const uint32_t*>(zeros), static_cast<uint16_t*>(y), (int)T, (int)N,
+                                   (int)K, hs, ga, epi);
+        if (st) return st;
+        return hipGetLastError() == hipSuccess ? QUICK_OK : QUICK_ERR_HIP;
+    }
     // the two launches write disjoint rows of y; the second reuses the
     // workspace after the first (same stream; stream-K leaves its counters
     // zero)

@@ -63,6 +63,11 @@ struct WsplitPlan {
 int launch_wsplit(const WsplitPlan& wp, const uint16_t* x, const lu4_t* pw, const uint16_t* ps, const uint32_t* pz,
                   uint16_t* y, float* ws, int M, int N, int K, hipStream_t st, const Epi& epi);
 
+// ... its grouped form (M = token rows; wp.split is 1).
+int launch_wsplit_grouped(const WsplitPlan& wp, const uint16_t* x, const lu4_t* pw, const uint16_t* ps,
+                          const uint32_t* pz, uint16_t* y, int M, int N, int K, hipStream_t st, const GroupArgs& ga,
+                          const Epi& epi);
+
 // Stream-kernel part.
 int launch_stream(const Plan& pl, const uint16_t* x, const lu4_t* pw, const uint16_t* ps, const uint32_t* pz,
                   uint16_t* y, int M, int N, int K, hipStream_t st, const Epi& epi);
