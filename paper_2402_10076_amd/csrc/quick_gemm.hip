@@ -1721,49 +1721,51 @@ tiled32_kernel(const uint16_t* __restrict__ x, const u4_t* __restrict__ pw,
     X(1, 2, 1, 4, 4, 2.5f, 0.118f) \
     X(1, 3, 1, 4, 2, 2.0f, 0.169f) \
     X(1, 4, 1, 4, 2, 2.5f, 0.208f) \
-    X(2, 1, 1, 4, 2, 2.5f, 0.127f) \
-    X(2, 2, 1, 4, 2, 3.0f, 0.161f) \
-    X(2, 3, 1, 4, 2, 3.5f, 0.198f) \
-    X(2, 4, 2, 4, 2, 3.0f, 0.484f) \
-    X(3, 2, 1, 2, 2, 3.0f, 0.189f) \
-    X(3, 3, 2, 4, 2, 4.0f, 0.397f) \
-    X(3, 4, 2, 4, 2, 4.5f, 0.529f) \
-    X(4, 1, 1, 2, 2, 2.5f, 0.183f) \
-    X(4, 2, 1, 2, 2, 3.0f, 0.219f) \
-    X(4, 3, 1, 2, 2, 3.5f, 0.252f) \
-    X(4, 4, 1, 2, 2, 4.5f, 0.292f) \
-    X(4, 2, 2, 4, 2, 3.5f, 0.328f) \
-    X(4, 3, 2, 4, 2, 4.5f, 0.430f) \
-    X(4, 3, 4, 4, 2, 4.0f, 0.743f) \
-    X(5, 2, 2, 2, 2, 3.5f, 0.433f) \
-    X(5, 3, 2, 2, 2, 5.0f, 0.519f) \
-    X(5, 4, 4, 4, 2, 7.0f, 1.165f) \
-    X(5, 4, 8, 4, 2, 5.5f, 2.303f) \
-    X(6, 2, 4, 4, 2, 4.5f, 0.723f) \
-    X(6, 3, 2, 2, 2, 5.5f, 0.603f) \
-    X(6, 3, 4, 4, 2, 6.5f, 1.018f) \
-    X(6, 4, 4, 4, 2, 8.0f, 1.272f) \
-    X(6, 4, 8, 4, 2, 7.0f, 2.481f) \
-    X(8, 1, 4, 4, 2, 3.5f, 0.560f) \
-    X(8, 2, 4, 4, 2, 5.5f, 0.864f) \
-    X(8, 3, 4, 4, 2, 7.5f, 1.213f) \
-    X(8, 2, 8, 4, 2, 5.0f, 1.560f) \
-    X(8, 3, 8, 4, 2, 6.5f, 2.301f) \
-    X(8, 4, 8, 4, 2, 8.5f, 2.973f)
-// ... of its grouped form (even n-tiles per wave: a gate tile with its up tile).
+    X(2, 1, 1, 4, 2, 2.0f, 0.132f) \
+    X(2, 2, 1, 4, 2, 2.5f, 0.162f) \
+    X(2, 3, 1, 4, 2, 3.0f, 0.205f) \
+    X(2, 2, 2, 4, 2, 2.0f, 0.272f) \
+    X(2, 4, 2, 4, 2, 2.5f, 0.472f) \
+    X(3, 2, 1, 2, 2, 2.5f, 0.205f) \
+    X(3, 3, 2, 4, 2, 4.0f, 0.396f) \
+    X(3, 4, 2, 4, 2, 5.0f, 0.485f) \
+    X(4, 1, 1, 2, 2, 2.5f, 0.193f) \
+    X(4, 2, 1, 2, 2, 3.0f, 0.227f) \
+    X(4, 3, 1, 2, 2, 3.5f, 0.262f) \
+    X(4, 4, 1, 2, 2, 4.5f, 0.304f) \
+    X(4, 2, 2, 4, 2, 3.5f, 0.346f) \
+    X(4, 3, 2, 4, 2, 4.5f, 0.440f) \
+    X(4, 2, 4, 4, 2, 3.5f, 0.514f) \
+    X(4, 3, 4, 4, 2, 4.5f, 0.715f) \
+    X(5, 3, 2, 2, 2, 5.0f, 0.548f) \
+    X(5, 4, 4, 4, 2, 7.5f, 1.114f) \
+    X(6, 2, 4, 4, 2, 5.0f, 0.720f) \
+    X(6, 3, 4, 4, 2, 7.0f, 0.994f) \
+    X(6, 4, 4, 4, 2, 8.0f, 1.239f) \
+    X(6, 4, 8, 4, 2, 7.0f, 2.326f) \
+    X(7, 2, 4, 4, 2, 6.0f, 0.779f) \
+    X(7, 3, 4, 4, 2, 8.5f, 1.089f) \
+    X(7, 2, 8, 4, 2, 5.0f, 1.338f) \
+    X(7, 3, 8, 4, 2, 6.5f, 1.973f) \
+    X(7, 4, 8, 4, 2, 8.0f, 2.536f) \
+    X(8, 2, 4, 4, 2, 6.0f, 0.856f) \
+    X(8, 3, 4, 4, 2, 7.5f, 1.207f) \
+    X(8, 2, 8, 4, 2, 5.5f, 1.469f) \
+    X(8, 3, 8, 4, 2, 7.5f, 2.145f) \
+    X(8, 4, 8, 4, 2, 9.0f, 2.766f)
+// ... of its grouped form (even n-tiles per wave: a gate tile with its up tile),
+// with the blocks, us per launch and us per k-group of its lower tiles.
 #define QUICK_WSPLIT_GRP_SHAPES(X) \
-    X(1, 2, 1, 4, 4, 2.5f, 0.118f) \
-    X(1, 4, 1, 4, 2, 2.5f, 0.208f) \
-    X(2, 4, 2, 4, 2, 3.0f, 0.484f) \
-    X(3, 4, 2, 4, 2, 4.5f, 0.529f) \
-    X(4, 2, 2, 4, 2, 3.5f, 0.328f) \
-    X(4, 4, 4, 4, 2, 5.5f, 0.990f) \
-    X(5, 4, 4, 4, 2, 7.0f, 1.165f) \
-    X(5, 4, 8, 4, 2, 5.5f, 2.303f) \
-    X(6, 4, 4, 4, 2, 8.0f, 1.272f) \
-    X(8, 2, 4, 4, 2, 5.5f, 0.864f) \
-    X(8, 2, 8, 4, 2, 5.0f, 1.560f) \
-    X(8, 4, 8, 4, 2, 8.5f, 2.973f)
+    X(1, 2, 1, 4, 4, 2.5f, 0.118f, 1, 2.5f, 0.118f) \
+    X(1, 4, 1, 4, 2, 2.5f, 0.208f, 1, 2.5f, 0.208f) \
+    X(2, 4, 2, 4, 2, 2.5f, 0.472f, 1, 2.5f, 0.472f) \
+    X(3, 4, 2, 4, 2, 5.0f, 0.485f, 2, 2.5f, 0.472f) \
+    X(4, 4, 4, 4, 2, 5.5f, 0.970f, 2, 5.0f, 0.750f) \
+    X(6, 4, 4, 4, 2, 8.0f, 1.239f, 4, 5.5f, 0.970f) \
+    X(8, 2, 4, 4, 2, 6.0f, 0.856f, 5, 4.5f, 0.660f) \
+    X(5, 4, 4, 4, 2, 7.5f, 1.114f, 2, 5.0f, 0.750f) \
+    X(8, 2, 8, 4, 2, 5.5f, 1.469f, 5, 5.0f, 1.200f) \
+    X(8, 4, 8, 4, 2, 9.0f, 2.766f, 5, 6.5f, 2.134f)
 
 #if QUICK_WSPLIT || QUICK_WSPLIT_GRP
 // ---------------------------------------------------------------------------
@@ -1771,10 +1773,20 @@ tiled32_kernel(const uint16_t* __restrict__ x, const u4_t* __restrict__ pw,
 // ---------------------------------------------------------------------------
 constexpr int kWsWaves = 8;
 
-template <int MTT, int NP, int NW, int RH, int DW, bool GRP = false>
-__global__ void __launch_bounds__(64 * kWsWaves)
-wsplit_kernel(const uint16_t* x, const u4_t* pw, const uint16_t* ps, const uint32_t* pz, uint16_t* y, float* ws, int M,
-              int N, int K, int kgps, int n_mtiles, int n_cg, int S, GroupArgs ga, Epi epi)
+// The LDS of a workgroup: one object per activation slot, so that the compiler
+// can tell a copy into one from reads of another.
+struct WsLds {
+    uint8_t *s0, *s1, *s2, *s3;
+    int* last_arrival;
+};
+
+// One tile: rows m0 .. mend (at most 16 * MTT), the n-tiles of column group
+// cg, the nks k-groups from kb0 on (slice s of S).
+template <int MTT, int NP, int NW, int RH, int DW, bool GRP>
+__device__ __forceinline__ void wsplit_tile(const WsLds& lds, const uint16_t* x, const u4_t* pw, const uint16_t* ps,
+                                            const uint32_t* pz, uint16_t* y, float* ws, int M, int N, int K, int m0,
+                                            int mend, int cg, int tin, int kb0, int nks, int s, int S, const int* rows,
+                                            const Epi& epi)
 {
     constexpr int WAVES = kWsWaves;
     constexpr int KW = WAVES / NW;               // K ranges
@@ -1784,14 +1796,9 @@ wsplit_kernel(const uint16_t* x, const u4_t* pw, const uint16_t* ps, const uint3
     constexpr int PA = (NP + 1) / 2, PB = NP - PA;
     static_assert(RH == 2 || (RH == 4 && DW % 2 == 0), "static slots over the unrolled k-groups");
     static_assert(DW >= 2, "weights are requested at least one k-group ahead");
-    __shared__ __attribute__((aligned(1024))) uint8_t lds_s0[STAGE];
-    __shared__ __attribute__((aligned(1024))) uint8_t lds_s1[STAGE];
-    __shared__ __attribute__((aligned(1024))) uint8_t lds_s2[RH > 2 ? STAGE : 16];
-    __shared__ __attribute__((aligned(1024))) uint8_t lds_s3[RH > 2 ? STAGE : 16];
-    __shared__ int last_arrival;
     auto stage_ptr = [&](int st) -> uint8_t* {
-        if constexpr (RH == 2) return st == 0 ? lds_s0 : lds_s1;
-        else return st == 0 ? lds_s0 : st == 1 ? lds_s1 : st == 2 ? lds_s2 : lds_s3;
+        if constexpr (RH == 2) return st == 0 ? lds.s0 : lds.s1;
+        else return st == 0 ? lds.s0 : st == 1 ? lds.s1 : st == 2 ? lds.s2 : lds.s3;
     };
     const int KG = K >> 7;
     const int NT = N >> 4;
@@ -1801,76 +1808,8 @@ wsplit_kernel(const uint16_t* x, const u4_t* pw, const uint16_t* ps, const uint3
     const int nw = wave - kw * NW;   // column group of this wave
     const int c = lane & 15;
     const int g = lane >> 4;
-
-    // ---- the workgroup's tile.  Consecutive tiles (M fastest, then N, then
-    // K slices; grouped: expert, N, the expert's M) run on one XCD and share
-    // weights in its L2.
-    int m0, mend = M, cg, s = 0, tin;
-    if constexpr (GRP) {
-        // per expert its routed rows [g_lo, g_hi) and the number of BM-row
-        // tiles of all experts before it, as in tiled_kernel
-        __shared__ int g_lo[kMaxExperts + 1], g_hi[kMaxExperts + 1], g_cum[kMaxExperts + 1];
-        if (wave == 0) {
-            int carry = 0;
-            for (int e0 = 0; e0 < ga.experts; e0 += 64) {
-                const int e = e0 + lane;
-                int lo = 0, hi = 0;
-                if (e < ga.experts) {
-                    lo = min(max(ga.offsets[e], 0), ga.routed);
-                    hi = min(max(ga.offsets[e + 1], lo), ga.routed);
-                }
-                int n = (hi - lo + MTT * 16 - 1) / (MTT * 16);
-#pragma unroll
-                for (int d = 1; d < 64; d <<= 1) {
-                    const int v = __shfl_up(n, d, 64);
-                    if (lane >= d) n += v;
-                }
-                if (e < ga.experts) {
-                    g_lo[e] = lo;
-                    g_hi[e] = hi;
-                    g_cum[e + 1] = carry + n;
-                }
-                carry += __shfl(n, 63, 64);
-            }
-            if (lane == 0) g_cum[0] = 0;
-        }
-        __syncthreads();
-        // the grid covers the host's upper bound; the tiles there are go
-        // evenly over the XCDs
-        const int tiles = (int)uniform(g_cum[ga.experts]) * n_cg;
-        const int per = (tiles + 7) >> 3;
-        tin = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
-        if ((int)(blockIdx.x >> 3) >= per || tin >= tiles) return;
-        int lo = 0, hi = ga.experts;   // the last e with g_cum[e] * n_cg <= tin
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (g_cum[mid] * n_cg <= tin) lo = mid;
-            else hi = mid;
-        }
-        const int e = uniform(lo);
-        const int local = tin - (int)uniform(g_cum[e]) * n_cg;
-        const int tiles_e = (int)uniform(g_cum[e + 1] - g_cum[e]);
-        cg = local / tiles_e;
-        m0 = (int)uniform(g_lo[e]) + (local - cg * tiles_e) * (MTT * 16);
-        mend = uniform(g_hi[e]);
-        const size_t units = (size_t)(N >> 4) * (K >> 7);   // of one expert
-        pw += (size_t)e * units * 64;
-        ps += (size_t)e * units * 16;
-        pz += (size_t)e * units * 2;
-        if (epi.bias) epi.bias += (size_t)e * N;
-    } else {
-        const int t = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-        const int tiles = n_mtiles * n_cg;
-        if (t >= tiles * S) return;
-        s = t / tiles;
-        tin = t - s * tiles;
-        cg = tin / n_mtiles;
-        m0 = (tin - cg * n_mtiles) * (MTT * 16);
-    }
     const int ntg = cg * (NW * NP);          // first n-tile of the workgroup
     const int nt0 = ntg + nw * NP;           // ... of this wave
-    const int kb0 = s * kgps;
-    const int nks = min(KG, kb0 + kgps) - kb0;
     const int kb = kb0 + nks * kw / KW;
     const int nk = kb0 + nks * (kw + 1) / KW - kb;
 
@@ -1892,7 +1831,7 @@ wsplit_kernel(const uint16_t* x, const u4_t* pw, const uint16_t* ps, const uint3
         const int ii = copy_of(i);
         int row = min(m0 + ii * 8 + (lane >> 3), mend - 1);
         if constexpr (GRP) {
-            if (ga.rows) row = ga.rows[row];   // gather
+            if (rows) row = rows[row];   // gather
             row = min(max(row, 0), M - 1);
         }
         vx[i] = (uint32_t)row * (uint32_t)K * 2 + (((lane & 7) ^ (4 * (ii & 1) + (lane >> 4))) << 4);
@@ -2163,10 +2102,10 @@ wsplit_kernel(const uint16_t* x, const u4_t* pw, const uint16_t* ps, const uint3
         wait_all();
         __syncthreads();
         if (threadIdx.x == 0)
-            last_arrival = __hip_atomic_fetch_add(&counters[tin], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+            *lds.last_arrival = __hip_atomic_fetch_add(&counters[tin], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
                            (unsigned)(S - 1);
         __syncthreads();
-        if (!last_arrival) return;
+        if (!*lds.last_arrival) return;
         each([&](f4_t (&v)[GP], int m, int nt) {
 #pragma unroll
             for (int h = 0; h < GP; ++h) {
@@ -2195,6 +2134,106 @@ wsplit_kernel(const uint16_t* x, const u4_t* pw, const uint16_t* ps, const uint3
         for (int h = 0; h < GP; ++h)
             if (nt + h < NT) store_out(y, epi, m, N, (nt + h) * 16 + 4 * g, v[h]);
     });
+}
+
+// MTB: the height (in 16-row blocks) of the lower tiles of the grouped form; 0
+// otherwise.
+template <int MTT, int NP, int NW, int RH, int DW, int MTB = 0>
+__global__ void __launch_bounds__(64 * kWsWaves)
+wsplit_kernel(const uint16_t* x, const u4_t* pw, const uint16_t* ps, const uint32_t* pz, uint16_t* y, float* ws, int M,
+              int N, int K, int kgps, int n_mtiles, int n_cg, int S, GroupArgs ga, Epi epi)
+{
+    constexpr bool GRP = MTB > 0;
+    constexpr int STAGE = kWsWaves / NW * MTT * 2048;
+    __shared__ __attribute__((aligned(1024))) uint8_t lds_s0[STAGE];
+    __shared__ __attribute__((aligned(1024))) uint8_t lds_s1[STAGE];
+    __shared__ __attribute__((aligned(1024))) uint8_t lds_s2[RH > 2 ? STAGE : 16];
+    __shared__ __attribute__((aligned(1024))) uint8_t lds_s3[RH > 2 ? STAGE : 16];
+    __shared__ int last_arrival;
+    const WsLds lds{lds_s0, lds_s1, lds_s2, lds_s3, &last_arrival};
+    const int KG = K >> 7;
+
+    // ---- the workgroup's tile.  Consecutive tiles (M fastest, then N, then
+    // K slices; grouped: expert, N, the expert's M) run on one XCD and share
+    // weights in its L2.
+    int m0, mend, cg, s = 0, tin;
+    if constexpr (GRP) {
+        // per expert its routed rows [g_lo, g_hi) and the number of BM-row
+        // tiles of all experts before it, as in tiled_kernel
+        __shared__ int g_lo[kMaxExperts + 1], g_hi[kMaxExperts + 1], g_cum[kMaxExperts + 1];
+        const int lane = threadIdx.x & 63;
+        if (threadIdx.x < 64) {
+            int carry = 0;
+            for (int e0 = 0; e0 < ga.experts; e0 += 64) {
+                const int e = e0 + lane;
+                int lo = 0, hi = 0;
+                if (e < ga.experts) {
+                    lo = min(max(ga.offsets[e], 0), ga.routed);
+                    hi = min(max(ga.offsets[e + 1], lo), ga.routed);
+                }
+                int n = (hi - lo + MTT * 16 - 1) / (MTT * 16);
+#pragma unroll
+                for (int d = 1; d < 64; d <<= 1) {
+                    const int v = __shfl_up(n, d, 64);
+                    if (lane >= d) n += v;
+                }
+                if (e < ga.experts) {
+                    g_lo[e] = lo;
+                    g_hi[e] = hi;
+                    g_cum[e + 1] = carry + n;
+                }
+                carry += __shfl(n, 63, 64);
+            }
+            if (lane == 0) g_cum[0] = 0;
+        }
+        __syncthreads();
+        // the grid covers the host's upper bound; the tiles there are go
+        // evenly over the XCDs
+        const int tiles = (int)uniform(g_cum[ga.experts]) * n_cg;
+        const int per = (tiles + 7) >> 3;
+        tin = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+        if ((int)(blockIdx.x >> 3) >= per || tin >= tiles) return;
+        int lo = 0, hi = ga.experts;   // the last e with g_cum[e] * n_cg <= tin
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (g_cum[mid] * n_cg <= tin) lo = mid;
+            else hi = mid;
+        }
+        const int e = uniform(lo);
+        const int local = tin - (int)uniform(g_cum[e]) * n_cg;
+        const int tiles_e = (int)uniform(g_cum[e + 1] - g_cum[e]);
+        cg = local / tiles_e;
+        // the expert's rows go evenly over its tiles
+        const int first = (int)uniform(g_lo[e]), n = (int)uniform(g_hi[e]) - first;
+        const int mi = local - cg * tiles_e;
+        m0 = first + (int)((int64_t)n * mi / tiles_e);
+        mend = first + (int)((int64_t)n * (mi + 1) / tiles_e);
+        const size_t units = (size_t)(N >> 4) * (K >> 7);   // of one expert
+        pw += (size_t)e * units * 64;
+        ps += (size_t)e * units * 16;
+        pz += (size_t)e * units * 2;
+        if (epi.bias) epi.bias += (size_t)e * N;
+    } else {
+        const int t = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+        const int tiles = n_mtiles * n_cg;
+        if (t >= tiles * S) return;
+        s = t / tiles;
+        tin = t - s * tiles;
+        cg = tin / n_mtiles;
+        m0 = (tin - cg * n_mtiles) * (MTT * 16);
+        mend = min(M, m0 + MTT * 16);
+    }
+    const int kb0 = s * kgps;
+    const int nks = min(KG, kb0 + kgps) - kb0;
+    if constexpr (GRP && MTB < MTT) {
+        if (mend - m0 <= MTB * 16) {
+            wsplit_tile<MTB, NP, NW, RH, DW, GRP>(lds, x, pw, ps, pz, y, ws, M, N, K, m0, mend, cg, tin, kb0, nks, s, S,
+                                                  ga.rows, epi);
+            return;
+        }
+    }
+    wsplit_tile<MTT, NP, NW, RH, DW, GRP>(lds, x, pw, ps, pz, y, ws, M, N, K, m0, mend, cg, tin, kb0, nks, s, S,
+                                          ga.rows, epi);
 }
 #endif  // QUICK_WSPLIT || QUICK_WSPLIT_GRP
 
@@ -2934,7 +2973,7 @@ extern "C" int quick_dev_wsplit(const void* x, const void* packed, const void* s
 #endif  // QUICK_WSPLIT
 
 #if QUICK_WSPLIT_GRP
-template <int MTT, int NP, int NW, int RH, int DW>
+template <int MTT, int NP, int NW, int RH, int DW, int MTB>
 void launch_wsplit_grp_t(const uint16_t* x, const u4_t* pw, const uint16_t* ps, const uint32_t* pz, uint16_t* y, int M,
                          int N, int K, hipStream_t st, const GroupArgs& ga, const Epi& epi)
 {
@@ -2942,7 +2981,7 @@ void launch_wsplit_grp_t(const uint16_t* x, const u4_t* pw, const uint16_t* ps, 
     const int64_t nm = ((int64_t)ga.routed + (int64_t)ga.experts * (MTT * 16 - 1)) / (MTT * 16);
     const int ncg = ceil_div(N / 16, NP * NW);
     const dim3 grid((unsigned)ceil_div(nm * ncg, 8) * 8);
-    hipLaunchKernelGGL((wsplit_kernel<MTT, NP, NW, RH, DW, true>), grid, dim3(64 * kWsWaves), 0, st, x, pw, ps, pz, y,
+    hipLaunchKernelGGL((wsplit_kernel<MTT, NP, NW, RH, DW, MTB>), grid, dim3(64 * kWsWaves), 0, st, x, pw, ps, pz, y,
                        (float*)nullptr, M, N, K, K / 128, 0, ncg, 1, ga, epi);
 }
 
@@ -2950,10 +2989,10 @@ int launch_wsplit_grouped(const WsplitPlan& wp, const uint16_t* x, const u4_t* p
                           const uint32_t* pz, uint16_t* y, int M, int N, int K, hipStream_t st, const GroupArgs& ga,
                           const Epi& epi)
 {
-#define QUICK_WS(MTT, NP, NW, RH, DW, F, S)                                                 \
-    if (wp.mt == MTT && wp.np == NP && wp.nw == NW) {                                       \
-        launch_wsplit_grp_t<MTT, NP, NW, RH, DW>(x, pw, ps, pz, y, M, N, K, st, ga, epi);   \
-        return QUICK_OK;                                                                    \
+#define QUICK_WS(MTT, NP, NW, RH, DW, F, S, MTB, FB, SB)                                         \
+    if (wp.mt == MTT && wp.np == NP && wp.nw == NW) {                                            \
+        launch_wsplit_grp_t<MTT, NP, NW, RH, DW, MTB>(x, pw, ps, pz, y, M, N, K, st, ga, epi);   \
+        return QUICK_OK;                                                                         \
     }
     QUICK_WSPLIT_GRP_SHAPES(QUICK_WS)
 #undef QUICK_WS
@@ -3003,8 +3042,8 @@ constexpr int kWsCus = 256;
 double wsplit_us(const WsShape& w, int64_t tiles, int64_t kg)
 {
     const int64_t full = tiles / kWsCus, rest = tiles % kWsCus;
-    const double rounds = (double)full + (rest ? 0.8 + 0.2 * (double)rest / kWsCus : 0.0);
-    return w.fixed + rounds * (double)kg * w.per_kg + 0.9 * w.fixed * (double)((tiles + kWsCus - 1) / kWsCus - 1);
+    const double rounds = (double)full + (rest ? 0.9 + 0.1 * (double)rest / kWsCus : 0.0);
+    return (double)((tiles + kWsCus - 1) / kWsCus) * w.fixed + rounds * (double)kg * w.per_kg;
 }
 
 // M <= 16: whether the wave-split form (one 16-row block) is the faster one.
@@ -3059,10 +3098,14 @@ bool wsplit_plan(int64_t M, int64_t N, int64_t K, const Plan& pl, size_t ws_byte
 }
 
 // The same for R routed rows over E experts, whose counts only the device
-// knows: the m-tiles are those of counts spread about the mean as under
-// uniform routing (standard deviation sqrt(mean)).
-constexpr WsShape kWsGrpShapes[] = {
-#define QUICK_WS(MTT, NP, NW, RH, DW, F, S) WsShape{MTT, NP, NW, F, S},
+// knows: taken to spread about the mean as under uniform routing (standard
+// deviation sqrt(mean)), each expert's rows going evenly over its tiles, on
+// lower tiles where they fit those.
+struct WsGrpShape {
+    WsShape hi, lo;
+};
+constexpr WsGrpShape kWsGrpShapes[] = {
+#define QUICK_WS(MTT, NP, NW, RH, DW, F, S, MTB, FB, SB) WsGrpShape{{MTT, NP, NW, F, S}, {MTB, NP, NW, FB, SB}},
     QUICK_WSPLIT_GRP_SHAPES(QUICK_WS)
 #undef QUICK_WS
 };
@@ -3071,19 +3114,26 @@ WsplitPlan wsplit_grouped_plan(int64_t R, int64_t E, int64_t N, int64_t K)
 {
     const double mean = (double)R / (double)E, dev = std::sqrt(mean);
     static const double at[4] = {-1.5, -0.5, 0.5, 1.5}, weight[4] = {0.13, 0.37, 0.37, 0.13};
+    const int64_t kg = K / 128;
     double best = 0;
-    WsplitPlan out{0, 0, 0, 1, (int)(K / 128)};
-    for (const WsShape& w : kWsGrpShapes) {
-        double per = 0;
-        for (int i = 0; i < 4; ++i) per += weight[i] * std::ceil(std::max(1.0, mean + at[i] * dev) / (16.0 * w.mt));
-        const int64_t nm = (int64_t)std::ceil(std::min(per, mean) * (double)E);
-        const int64_t tiles = nm * ((N / 16 + w.np * w.nw - 1) / (w.np * w.nw));
-        const double us = wsplit_us(w, tiles, K / 128);
+    WsplitPlan out{0, 0, 0, 1, (int)kg};
+    for (const WsGrpShape& w : kWsGrpShapes) {
+        double hi = 0, lo = 0;   // tiles per expert
+        for (int i = 0; i < 4; ++i) {
+            const double rows = std::max(1.0, mean + at[i] * dev), n = std::ceil(rows / (16.0 * w.hi.mt));
+            (std::ceil(rows / n) <= 16.0 * w.lo.mt ? lo : hi) += weight[i] * n;
+        }
+        // experts without a row have no tile
+        const double some = std::min(1.0, mean);
+        const int64_t ncg = (N / 16 + w.hi.np * w.hi.nw - 1) / (w.hi.np * w.hi.nw);
+        const int64_t tiles = (int64_t)std::ceil((hi + lo) * some * (double)E) * ncg;
+        const double part = hi / (hi + lo);
+        const double us = part * wsplit_us(w.hi, tiles, kg) + (1.0 - part) * wsplit_us(w.lo, tiles, kg);
         if (!out.mt || us < best) {
             best = us;
-            out.mt = w.mt;
-            out.np = w.np;
-            out.nw = w.nw;
+            out.mt = w.hi.mt;
+            out.np = w.hi.np;
+            out.nw = w.hi.nw;
         }
     }
     return out;
