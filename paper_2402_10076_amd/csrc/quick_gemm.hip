@@ -1716,56 +1716,57 @@ tiled32_kernel(const uint16_t* __restrict__ x, const u4_t* __restrict__ pw,
 [[maybe_unused]] constexpr int kWsReduceSplit = 4;
 // Shapes of the wave-split kernel: X(16-row blocks per workgroup, n-tiles per
 // wave, waves side by side along N, activation slots in halves of a k-group,
-// weight slots in k-groups, us per launch, us per k-group).
+// weight slots in k-groups, us per launch, us per further round of workgroups,
+// us per k-group).
 #define QUICK_WSPLIT_SHAPES(X) \
-    X(1, 2, 1, 4, 4, 2.5f, 0.118f) \
-    X(1, 3, 1, 4, 2, 2.0f, 0.169f) \
-    X(1, 4, 1, 4, 2, 2.5f, 0.208f) \
-    X(2, 1, 1, 4, 2, 2.0f, 0.132f) \
-    X(2, 2, 1, 4, 2, 2.5f, 0.162f) \
-    X(2, 3, 1, 4, 2, 3.0f, 0.205f) \
-    X(2, 2, 2, 4, 2, 2.0f, 0.272f) \
-    X(2, 4, 2, 4, 2, 2.5f, 0.472f) \
-    X(3, 2, 1, 2, 2, 2.5f, 0.205f) \
-    X(3, 3, 2, 4, 2, 4.0f, 0.396f) \
-    X(3, 4, 2, 4, 2, 5.0f, 0.485f) \
-    X(4, 1, 1, 2, 2, 2.5f, 0.193f) \
-    X(4, 2, 1, 2, 2, 3.0f, 0.227f) \
-    X(4, 3, 1, 2, 2, 3.5f, 0.262f) \
-    X(4, 4, 1, 2, 2, 4.5f, 0.304f) \
-    X(4, 2, 2, 4, 2, 3.5f, 0.346f) \
-    X(4, 3, 2, 4, 2, 4.5f, 0.440f) \
-    X(4, 2, 4, 4, 2, 3.5f, 0.514f) \
-    X(4, 3, 4, 4, 2, 4.5f, 0.715f) \
-    X(5, 3, 2, 2, 2, 5.0f, 0.548f) \
-    X(5, 4, 4, 4, 2, 7.5f, 1.114f) \
-    X(6, 2, 4, 4, 2, 5.0f, 0.720f) \
-    X(6, 3, 4, 4, 2, 7.0f, 0.994f) \
-    X(6, 4, 4, 4, 2, 8.0f, 1.239f) \
-    X(6, 4, 8, 4, 2, 7.0f, 2.326f) \
-    X(7, 2, 4, 4, 2, 6.0f, 0.779f) \
-    X(7, 3, 4, 4, 2, 8.5f, 1.089f) \
-    X(7, 2, 8, 4, 2, 5.0f, 1.338f) \
-    X(7, 3, 8, 4, 2, 6.5f, 1.973f) \
-    X(7, 4, 8, 4, 2, 8.0f, 2.536f) \
-    X(8, 2, 4, 4, 2, 6.0f, 0.856f) \
-    X(8, 3, 4, 4, 2, 7.5f, 1.207f) \
-    X(8, 2, 8, 4, 2, 5.5f, 1.469f) \
-    X(8, 3, 8, 4, 2, 7.5f, 2.145f) \
-    X(8, 4, 8, 4, 2, 9.0f, 2.766f)
+    X(1, 2, 1, 4, 4, 3.0f, 0.6f, 0.129f) \
+    X(1, 3, 1, 4, 2, 3.0f, 0.6f, 0.161f) \
+    X(1, 4, 1, 4, 2, 3.0f, 0.6f, 0.218f) \
+    X(2, 1, 1, 4, 2, 2.0f, 2.0f, 0.132f) \
+    X(2, 2, 1, 4, 2, 2.5f, 2.5f, 0.162f) \
+    X(2, 3, 1, 4, 2, 3.0f, 3.0f, 0.205f) \
+    X(2, 2, 2, 4, 2, 2.0f, 2.0f, 0.272f) \
+    X(2, 4, 2, 4, 2, 2.5f, 2.5f, 0.472f) \
+    X(3, 2, 1, 2, 2, 2.5f, 2.5f, 0.205f) \
+    X(3, 3, 2, 4, 2, 4.0f, 4.0f, 0.396f) \
+    X(3, 4, 2, 4, 2, 5.0f, 5.0f, 0.485f) \
+    X(4, 1, 1, 2, 2, 2.5f, 2.5f, 0.193f) \
+    X(4, 2, 1, 2, 2, 3.0f, 3.0f, 0.227f) \
+    X(4, 3, 1, 2, 2, 3.5f, 3.5f, 0.262f) \
+    X(4, 4, 1, 2, 2, 4.5f, 4.5f, 0.304f) \
+    X(4, 2, 2, 4, 2, 3.5f, 3.5f, 0.346f) \
+    X(4, 3, 2, 4, 2, 4.5f, 4.5f, 0.440f) \
+    X(4, 2, 4, 4, 2, 3.5f, 3.5f, 0.514f) \
+    X(4, 3, 4, 4, 2, 4.5f, 4.5f, 0.715f) \
+    X(5, 3, 2, 2, 2, 5.0f, 5.0f, 0.548f) \
+    X(5, 4, 4, 4, 2, 7.5f, 7.5f, 1.114f) \
+    X(6, 2, 4, 4, 2, 5.0f, 5.0f, 0.720f) \
+    X(6, 3, 4, 4, 2, 7.0f, 7.0f, 0.994f) \
+    X(6, 4, 4, 4, 2, 8.0f, 8.0f, 1.239f) \
+    X(6, 4, 8, 4, 2, 7.0f, 7.0f, 2.326f) \
+    X(7, 2, 4, 4, 2, 6.0f, 6.0f, 0.779f) \
+    X(7, 3, 4, 4, 2, 8.5f, 8.5f, 1.089f) \
+    X(7, 2, 8, 4, 2, 5.0f, 5.0f, 1.338f) \
+    X(7, 3, 8, 4, 2, 6.5f, 6.5f, 1.973f) \
+    X(7, 4, 8, 4, 2, 8.0f, 8.0f, 2.536f) \
+    X(8, 2, 4, 4, 2, 6.0f, 6.0f, 0.856f) \
+    X(8, 3, 4, 4, 2, 7.5f, 7.5f, 1.207f) \
+    X(8, 2, 8, 4, 2, 5.5f, 5.5f, 1.469f) \
+    X(8, 3, 8, 4, 2, 7.5f, 7.5f, 2.145f) \
+    X(8, 4, 8, 4, 2, 9.0f, 9.0f, 2.766f)
 // ... of its grouped form (even n-tiles per wave: a gate tile with its up tile),
-// with the blocks, us per launch and us per k-group of its lower tiles.
+// with the 16-row blocks and us per k-group of its lower tiles.
 #define QUICK_WSPLIT_GRP_SHAPES(X) \
-    X(1, 2, 1, 4, 4, 2.5f, 0.118f, 1, 2.5f, 0.118f) \
-    X(1, 4, 1, 4, 2, 2.5f, 0.208f, 1, 2.5f, 0.208f) \
-    X(2, 4, 2, 4, 2, 2.5f, 0.472f, 1, 2.5f, 0.472f) \
-    X(3, 4, 2, 4, 2, 5.0f, 0.485f, 2, 2.5f, 0.472f) \
-    X(4, 4, 4, 4, 2, 5.5f, 0.970f, 2, 5.0f, 0.750f) \
-    X(6, 4, 4, 4, 2, 8.0f, 1.239f, 4, 5.5f, 0.970f) \
-    X(8, 2, 4, 4, 2, 6.0f, 0.856f, 5, 4.5f, 0.660f) \
-    X(5, 4, 4, 4, 2, 7.5f, 1.114f, 2, 5.0f, 0.750f) \
-    X(8, 2, 8, 4, 2, 5.5f, 1.469f, 5, 5.0f, 1.200f) \
-    X(8, 4, 8, 4, 2, 9.0f, 2.766f, 5, 6.5f, 2.134f)
+    X(1, 4, 1, 4, 2, 6.5f, 1.3f, 0.142f, 1, 0.142f) \
+    X(2, 4, 2, 4, 2, 5.5f, 1.1f, 0.371f, 1, 0.357f) \
+    X(3, 4, 2, 4, 2, 7.5f, 3.8f, 0.497f, 2, 0.417f) \
+    X(4, 2, 4, 4, 2, 4.5f, 0.9f, 0.560f, 2, 0.436f) \
+    X(5, 4, 4, 4, 2, 6.5f, 6.5f, 1.164f, 2, 0.761f) \
+    X(5, 4, 8, 4, 2, 5.5f, 5.5f, 2.149f, 2, 1.581f) \
+    X(6, 4, 8, 4, 2, 10.0f, 10.0f, 2.409f, 4, 1.861f) \
+    X(8, 2, 4, 4, 2, 3.5f, 3.5f, 0.969f, 5, 0.719f) \
+    X(8, 2, 8, 4, 2, 9.5f, 9.5f, 1.546f, 5, 1.047f) \
+    X(8, 4, 8, 4, 2, 11.5f, 11.5f, 2.795f, 5, 2.081f)
 
 #if QUICK_WSPLIT || QUICK_WSPLIT_GRP
 // ---------------------------------------------------------------------------
@@ -2944,7 +2945,7 @@ int launch_wsplit(const WsplitPlan& wp, const uint16_t* x, const u4_t* pw, const
                   uint16_t* y, float* ws, int M, int N, int K, hipStream_t st, const Epi& epi)
 {
     bool known = false;
-#define QUICK_WS(MTT, NP, NW, RH, DW, F, S)                                                  \
+#define QUICK_WS(MTT, NP, NW, RH, DW, F, NX, S)                                              \
     if (!known && wp.mt == MTT && wp.np == NP && wp.nw == NW) {                              \
         launch_wsplit_t<MTT, NP, NW, RH, DW>(wp, x, pw, ps, pz, y, ws, M, N, K, st, epi);    \
         known = true;                                                                        \
@@ -2959,17 +2960,6 @@ int launch_wsplit(const WsplitPlan& wp, const uint16_t* x, const u4_t* pw, const
     }
     return QUICK_OK;
 }
-#ifdef QUICK_DEV
-extern "C" int quick_dev_wsplit(const void* x, const void* packed, const void* scales, const void* zeros, void* y,
-                                int64_t M, int64_t N, int64_t K, void* ws, int mt, int np, int nw, int split, void* stream)
-{
-    const int kg = (int)(K / 128);
-    WsplitPlan wp{mt, np, nw, split, ceil_div(kg, split)};
-    wp.split = ceil_div(kg, wp.kgps);
-    return launch_wsplit(wp, (const uint16_t*)x, (const u4_t*)packed, (const uint16_t*)scales, (const uint32_t*)zeros,
-                         (uint16_t*)y, (float*)ws, (int)M, (int)N, (int)K, (hipStream_t)stream, Epi{nullptr, 0});
-}
-#endif
 #endif  // QUICK_WSPLIT
 
 #if QUICK_WSPLIT_GRP
@@ -2989,7 +2979,7 @@ int launch_wsplit_grouped(const WsplitPlan& wp, const uint16_t* x, const u4_t* p
                           const uint32_t* pz, uint16_t* y, int M, int N, int K, hipStream_t st, const GroupArgs& ga,
                           const Epi& epi)
 {
-#define QUICK_WS(MTT, NP, NW, RH, DW, F, S, MTB, FB, SB)                                         \
+#define QUICK_WS(MTT, NP, NW, RH, DW, F, NX, S, MTB, SB)                                         \
     if (wp.mt == MTT && wp.np == NP && wp.nw == NW) {                                            \
         launch_wsplit_grp_t<MTT, NP, NW, RH, DW, MTB>(x, pw, ps, pz, y, M, N, K, st, ga, epi);   \
         return QUICK_OK;                                                                         \
@@ -3016,23 +3006,24 @@ using quick::WsplitPlan;
 
 // Shape of a wave-split launch: the one whose estimated time is least.  The
 // estimate is
-//   fixed + rounds * k-groups * us per k-group + 0.9 * fixed per further round
-// with the two constants of each shape in QUICK_WSPLIT_SHAPES fitted to 5600
-// timings of the shapes over 115 random GEMMs (17 <= M <= 2048, N and K from
-// 1024, back to back so that the chip runs at its sustained clock), a last
-// round of r < 256 workgroups counted as 0.8 + 0.2 r / 256 of a full one (256
-// compute units, one workgroup each), and not under the time of reading the
-// weights at 4.2 TB/s.  Splitting K costs the traffic of its fp32 partial sums
-// and, from kWsReduceSplit slices on, a second launch.  On those GEMMs the
-// choice is on average 1 % (at most 18 %) slower than the best shape, and 1.25
-// times as fast as the tiled kernels on their own rules (1 % slower at worst).
-// A split uses no more workspace than `ws_bytes`, what the tiled plan needs.
+//   us per launch + further rounds * us per round + rounds * k-groups * us per k-group
+// with the constants of QUICK_WSPLIT_SHAPES fitted to 5200 timings of the
+// shapes over 105 random GEMMs (17 <= M <= 2048, N and K from 1024, back to
+// back so that the chip runs at its sustained clock, weights and activations
+// from HBM), a last round of r < 256 workgroups counted as 0.9 + 0.1 r / 256
+// of a full one (256 compute units, one workgroup each), and not under the time
+// of reading the weights at 4.2 TB/s.  Splitting K costs the traffic of its
+// fp32 partial sums and, from kWsReduceSplit slices on, a second launch.  On
+// those GEMMs the choice is on average 0.9 % (at most 7 %) slower than the best
+// shape, and 1.23 times as fast as the tiled kernels on their own rules (0.4 %
+// slower at worst).  A split uses no more workspace than `ws_bytes`, what the
+// tiled plan needs.
 struct WsShape {
     int mt, np, nw;
-    float fixed, per_kg;
+    float fixed, next, per_kg;
 };
 constexpr WsShape kWsShapes[] = {
-#define QUICK_WS(MTT, NP, NW, RH, DW, F, S) WsShape{MTT, NP, NW, F, S},
+#define QUICK_WS(MTT, NP, NW, RH, DW, F, NX, S) WsShape{MTT, NP, NW, F, NX, S},
     QUICK_WSPLIT_SHAPES(QUICK_WS)
 #undef QUICK_WS
 };
@@ -3043,7 +3034,7 @@ double wsplit_us(const WsShape& w, int64_t tiles, int64_t kg)
 {
     const int64_t full = tiles / kWsCus, rest = tiles % kWsCus;
     const double rounds = (double)full + (rest ? 0.9 + 0.1 * (double)rest / kWsCus : 0.0);
-    return (double)((tiles + kWsCus - 1) / kWsCus) * w.fixed + rounds * (double)kg * w.per_kg;
+    return w.fixed + (double)((tiles + kWsCus - 1) / kWsCus - 1) * w.next + rounds * (double)kg * w.per_kg;
 }
 
 // M <= 16: whether the wave-split form (one 16-row block) is the faster one.
@@ -3100,12 +3091,14 @@ bool wsplit_plan(int64_t M, int64_t N, int64_t K, const Plan& pl, size_t ws_byte
 // The same for R routed rows over E experts, whose counts only the device
 // knows: taken to spread about the mean as under uniform routing (standard
 // deviation sqrt(mean)), each expert's rows going evenly over its tiles, on
-// lower tiles where they fit those.
+// lower tiles where they fit those.  (Fitted to 38 grouped GEMMs, 4 to 16 experts
+// and 2 to 350 rows each: the choice is on average 1.3 %, at most 13 %, slower
+// than the best shape.)
 struct WsGrpShape {
     WsShape hi, lo;
 };
 constexpr WsGrpShape kWsGrpShapes[] = {
-#define QUICK_WS(MTT, NP, NW, RH, DW, F, S, MTB, FB, SB) WsGrpShape{{MTT, NP, NW, F, S}, {MTB, NP, NW, FB, SB}},
+#define QUICK_WS(MTT, NP, NW, RH, DW, F, NX, S, MTB, SB) WsGrpShape{{MTT, NP, NW, F, NX, S}, {MTB, NP, NW, F, NX, SB}},
     QUICK_WSPLIT_GRP_SHAPES(QUICK_WS)
 #undef QUICK_WS
 };
