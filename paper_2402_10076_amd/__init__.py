@@ -89,6 +89,8 @@ ACT_SILU_GATE = 1
 def lib():
     """The loaded library (raises if it has not been built)."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is None:
             if not os.path.exists(LIB_PATH):
@@ -236,7 +238,7 @@ def workspace_bytes(M: int, N: int, K: int, cfg: QuickConfig | None = None) -> i
 
 
 def _dptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
+    return t.data_ptr() if t is not None else None
 
 
 def _nbytes(t: torch.Tensor) -> int:
@@ -266,6 +268,9 @@ def _dev(what: str, name: str, t, ref: torch.Tensor, dtype=None, nbytes: int | N
 
 
 def _check_x(what: str, x, rows_name: str = "M"):
+    if (isinstance(x, torch.Tensor) and x.is_cuda and x.dtype is torch.float16 and x.dim() == 2
+            and x.is_contiguous()):
+        return
     if not isinstance(x, torch.Tensor) or x.device.type != _DEVICE_TYPE:
         raise QuickError(QUICK_ERR_INVALID_ARG, "%s: x must be a tensor on the GPU" % what)
     if x.dtype != torch.float16 or x.dim() != 2 or not x.is_contiguous():
@@ -285,6 +290,14 @@ def _weight_bytes(what: str, K: int, N: int, group: int):
 
 def _check_weights(what: str, x, packed, scales, zeros, K: int, N: int, group: int, experts: int = 1):
     wb, sb, zb = _weight_bytes(what, K, N, group)
+    # the checks of _dev below in one pass, for tensors on the GPU (a small
+    # call is bound by the host: 16 x 512 x 512 takes 3.5 us on the GPU)
+    if (isinstance(packed, torch.Tensor) and isinstance(scales, torch.Tensor) and isinstance(zeros, torch.Tensor)
+            and x.is_cuda and packed.is_cuda and scales.is_cuda and zeros.is_cuda
+            and x.get_device() == packed.get_device() == scales.get_device() == zeros.get_device()
+            and packed.is_contiguous() and scales.is_contiguous() and zeros.is_contiguous()
+            and packed.nbytes >= wb * experts and scales.nbytes >= sb * experts and zeros.nbytes >= zb * experts):
+        return
     _dev(what, "packed", packed, x, nbytes=wb * experts)
     _dev(what, "scales", scales, x, nbytes=sb * experts)
     _dev(what, "zeros", zeros, x, nbytes=zb * experts)
@@ -292,6 +305,8 @@ def _check_weights(what: str, x, packed, scales, zeros, K: int, N: int, group: i
 
 def _out(what: str, y, x, rows: int, cols: int):
     if y is None:
+        if type(x) is torch.Tensor:
+            return x.new_empty((rows, cols))
         return torch.empty((rows, cols), dtype=torch.float16, device=x.device)
     _dev(what, "y", y, x, dtype=torch.float16, shape=(rows, cols))
     return y
@@ -304,9 +319,17 @@ def _ws(what: str, workspace, x):
     return _nbytes(workspace)
 
 
+# handle of a device's current stream without building a torch.cuda.Stream
+# (0.1 against 1.9 us)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream, x):
-    st = stream if stream is not None else torch.cuda.current_stream(x.device)
-    return ctypes.c_void_p(st.cuda_stream)
+    if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream(x.get_device())
+        stream = torch.cuda.current_stream(x.device)
+    return stream.cuda_stream
 
 
 def w4a16_gemm(x: torch.Tensor, packed: torch.Tensor, scales: torch.Tensor, zeros: torch.Tensor,
