@@ -2357,18 +2357,24 @@ namespace {
 
 using quick::tiled_resident;
 
-// The stream kernel's automatic shape: 2 n-tiles per wave for wide N, and
-// waves per workgroup doubled while there are fewer than 2048 waves and
-// each keeps >= 2 k-groups.
-void stream_defaults(int64_t N, int64_t K, Plan* pl)
+// The stream kernel's automatic shape.  Two n-tiles per wave for wide N from 3
+// rows on (one activation read serves both: 22016 x 4096 at M = 4 13.0 against
+// 13.7 us), one below (at M = 1 12.1 against 12.6 us, 27648 x 5120 16.8
+// against 17.7).  Four waves per workgroup (57344 x 8192 at M = 1 44.4 against
+// 46.9 us with two), eight while there are fewer than 2048 waves or to keep
+// each wave's range within the single pass of 16 units (8880 x 11008 at M = 1
+// 14.9 against 16.5 us); every wave keeps >= 2 k-groups.
+void stream_defaults(int64_t M, int64_t N, int64_t K, Plan* pl)
 {
     const int64_t KG = K / 128;
     const int64_t NT = N / 16;
     pl->variant = kVariantStream;
-    pl->wn = NT / 2 >= 512 ? 2 : 1;
+    pl->wn = NT / 2 >= 512 && M > 2 ? 2 : 1;
     const int64_t wgs = (NT + pl->wn - 1) / pl->wn;
     int w = 1;
-    while (w < 8 && wgs * w < 2048 && KG / (2 * w) >= 2) w *= 2;
+    while (w < 8 && KG / (2 * w) >= 2 &&
+           (w < 4 || wgs * w < 2048 || (KG > 16 * w && KG <= 128)))
+        w *= 2;
     pl->split = w;
     pl->bm = 0;
     pl->kgps = 0;
@@ -2377,7 +2383,7 @@ void stream_defaults(int64_t N, int64_t K, Plan* pl)
 int auto_plan(int64_t M, int64_t N, int64_t K, Plan* pl)
 {
     const int64_t KG = K / 128;
-    auto stream_plan = [&]() { stream_defaults(N, K, pl); };
+    auto stream_plan = [&]() { stream_defaults(M, N, K, pl); };
     if (M <= 8) {
         // weights dominate; each wave streams its own k-range (no LDS tile)
         stream_plan();
@@ -2530,7 +2536,7 @@ int make_plan(int64_t M, int64_t N, int64_t K, const quick_config_t* cfg, Plan* 
     }
     if (cfg->variant == kVariantStream) {
         if (M > 64) return QUICK_ERR_INVALID_ARG;
-        if (pl->variant != kVariantStream) stream_defaults(N, K, pl);
+        if (pl->variant != kVariantStream) stream_defaults(M, N, K, pl);
         if (cfg->split_k) {
             if (cfg->split_k != 1 && cfg->split_k != 2 && cfg->split_k != 4 && cfg->split_k != 8)
                 return QUICK_ERR_INVALID_ARG;
