@@ -1719,11 +1719,11 @@ tiled32_kernel(const uint16_t* __restrict__ x, const u4_t* __restrict__ pw,
 // weight slots in k-groups, us per launch, us per further round of workgroups,
 // us per k-group).
 #define QUICK_WSPLIT_SHAPES(X) \
-    X(1, 2, 1, 4, 4, 3.0f, 0.6f, 0.129f) \
-    X(1, 3, 1, 4, 2, 3.0f, 0.6f, 0.161f) \
-    X(1, 4, 1, 4, 2, 3.0f, 0.6f, 0.218f) \
-    X(2, 1, 1, 4, 2, 2.0f, 2.0f, 0.132f) \
-    X(2, 2, 1, 4, 2, 2.5f, 2.5f, 0.162f) \
+    X(1, 2, 1, 2, 2, 3.0f, 0.6f, 0.129f) \
+    X(1, 3, 1, 2, 2, 3.0f, 0.6f, 0.161f) \
+    X(1, 4, 1, 2, 2, 3.0f, 0.6f, 0.218f) \
+    X(2, 1, 1, 2, 2, 2.0f, 2.0f, 0.132f) \
+    X(2, 2, 1, 2, 2, 2.5f, 2.5f, 0.162f) \
     X(2, 3, 1, 4, 2, 3.0f, 3.0f, 0.205f) \
     X(2, 2, 2, 4, 2, 2.0f, 2.0f, 0.272f) \
     X(2, 4, 2, 4, 2, 2.5f, 2.5f, 0.472f) \
@@ -1757,7 +1757,7 @@ tiled32_kernel(const uint16_t* __restrict__ x, const u4_t* __restrict__ pw,
 // ... of its grouped form (even n-tiles per wave: a gate tile with its up tile),
 // with the 16-row blocks and us per k-group of its lower tiles.
 #define QUICK_WSPLIT_GRP_SHAPES(X) \
-    X(1, 4, 1, 4, 2, 6.5f, 1.3f, 0.142f, 1, 0.142f) \
+    X(1, 4, 1, 2, 2, 6.5f, 1.3f, 0.142f, 1, 0.142f) \
     X(2, 4, 2, 4, 2, 5.5f, 1.1f, 0.371f, 1, 0.357f) \
     X(3, 4, 2, 4, 2, 7.5f, 3.8f, 0.497f, 2, 0.417f) \
     X(4, 2, 4, 4, 2, 4.5f, 0.9f, 0.560f, 2, 0.436f) \
