@@ -3051,9 +3051,19 @@ double wsplit_us(const WsShape& w, int64_t tiles, int64_t kg)
 // unit in three rounds: 18.6 against 16.5 us).  The sliced stream kernel wins
 // while its workgroups are a single round (12288 x 4096 at M = 10: 9.9
 // against 10.0 us; 15360 x 5120 at M = 16, 360 workgroups: 15.0 against 12.4
-// us); the 16-row tiles never do.
+// us).  The 16-row tiles win on the largest matrices where they fill their last
+// round of two workgroups per compute unit to three quarters (at M = 16, 57344 x
+// 8192, 448 of 512: 51.5 against 55.5 us, 152064 x 5120, 1188 of 1536: 88.6
+// against 97.8, 16384 x 28672 in 4 K slices, all 512: 53.2 against 55.3) and
+// lose where they do not (73728 x 12288, 576 of 1024: 110 against 104; 35840 x
+// 8192 in 2 slices, 560 of 1024: 43.3 against 36.1) or are few and short (8192 x
+// 1152: 7.9 against 4.5).
 bool wsplit_small_m(int64_t M, int64_t N, int64_t K, const Plan& pl)
 {
+    if (pl.variant == kVariantTiled && K * N / 2 >= ((int64_t)128 << 20)) {
+        const int64_t wgs = (int64_t)ceil_div(N, kTiledWaves * pl.wn) * pl.split, slots = 2 * kWsCus;
+        return wgs * 4 < (wgs + slots - 1) / slots * slots * 3;
+    }
     if (pl.variant == kVariantKStream) return (int64_t)ks_groups(N, pl.wn) * pl.split > kWsCus;
     if (pl.variant != kVariantStream) return true;
     const size_t xb = (size_t)pl.split * stream_slice_bytes((int)M, (int)(K / 128), pl.split);
