@@ -46,7 +46,34 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
+AUTO_KERNEL = "wave_stream_kernel"
+
+
+def selection(Q, p) -> dict:
+    """The plan of a point's launch; variant 0 where the launch is left to the
+    rules and runs in the wave-split form (recorded so in the tune table, or
+    more than 16 rows and no table)."""
+    if p["M"] > 16 and Q.tune_table_size() == 0:
+        return dict(variant=0, split_k=0, tile_m=0, tile_n=0)
+    return Q.select_config(p["M"], p["N"], p["K"])
+
+
+def fold_reductions(rows):
+    """Dispatches (id, kernel symbol, value) with each reduction pass that
+    follows a wave-split launch added to it: whether there is one is the
+    library's choice, so launch_sequence has no entry for it."""
+    out = []
+    for r in rows:
+        if out and "splitk_reduce_kernel" in r[1] and AUTO_KERNEL in out[-1][1]:
+            out[-1] = (out[-1][0], out[-1][1], out[-1][2] + r[2])
+        else:
+            out.append(r)
+    return out
+
+
 def kernel_name(sel: dict) -> str:
+    if sel["variant"] == 0:
+        return AUTO_KERNEL
     if sel["variant"] == 1:
         return "stream_kernel<MT,%d,%d>" % (sel["tile_n"], sel["split_k"])
     if sel["variant"] == 5:
@@ -71,7 +98,7 @@ def launch_sequence(points):
     seq = []
     for p in points:
         sel = p["sel"]
-        if sel["variant"] == 1:
+        if sel["variant"] in (0, 1):   # both symbols hold "stream_kernel<"
             seq.append((p["kernel"], "stream_kernel<"))
         elif sel["variant"] == 5:
             seq.append((p["kernel"], "kstream_kernel<%d>" % sel["tile_n"]))
@@ -150,8 +177,8 @@ def ingest_pmc(fetch_csv, write_csv, cal_fetch_csv, cal_write_csv, points, domin
     per = {}
     per_point = {}
     for name, path in (("FETCH_SIZE", fetch_csv), ("WRITE_SIZE", write_csv)):
-        ours = [r for r in read_counter_csv(path, name)
-                if "anonymous namespace)::" in r[1] and "at::" not in r[1]]
+        ours = fold_reductions([r for r in read_counter_csv(path, name)
+                                if "anonymous namespace)::" in r[1] and "at::" not in r[1]])
         # whole repetitions of the step's launch sequence from the start
         # (eager warm-up, graph replays, eager timing steps); the subset-graph
         # replays that follow are not used
@@ -224,6 +251,7 @@ def ingest_trace(trace_csv, points, dominant, out_md, command, run_log=""):
             rows.append((int(r["Dispatch_Id"]), r["Kernel_Name"],
                          (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) * 1e-3))
     rows.sort()
+    rows = fold_reductions(rows)
     # whole repetitions of the step from the start (eager warm-up, graph
     # replays, eager event steps); the subset-graph replays that follow are
     # not used
@@ -348,7 +376,7 @@ def gemm_counters(csv_path, points, counters):
             continue
         d = disp.setdefault(int(r["Dispatch_Id"]), {"name": name, "dur": dur})
         d[r["Counter_Name"]] = d.get(r["Counter_Name"], 0.0) + float(r["Counter_Value"])
-    ids = sorted(disp)
+    ids = [i for i, _, _ in fold_reductions([(i, disp[i]["name"], 0) for i in sorted(disp)])]
     names = [disp[i]["name"] for i in ids]
     reps = whole_repetitions(names, seq)
     if reps == 0:
@@ -876,7 +904,7 @@ def main():
         import workloads as W
         points = build_points([int(c) for c in args.configs.split(",") if c])
         for p in points:
-            p["sel"] = Q.select_config(p["M"], p["N"], p["K"])
+            p["sel"] = selection(Q, p)
             p["kernel"] = kernel_name(p["sel"])
             p["bytes"] = W.alg_bytes(p["M"], p["N"], p["K"])
             p["flops"] = W.flops(p["M"], p["N"], p["K"])
@@ -889,7 +917,7 @@ def main():
         import paper_2402_10076_amd as Q
         points = build_points([int(c) for c in args.configs.split(",") if c])
         for p in points:
-            p["sel"] = Q.select_config(p["M"], p["N"], p["K"])
+            p["sel"] = selection(Q, p)
             p["kernel"] = kernel_name(p["sel"])
         cmd = ("rocprofv3 --pmc " + " ".join(WAIT_COUNTERS) + " --output-format csv -d <dir> -o sq "
                "-- python3 <repo>/bench.py --steps 1 --warmup 0 --no-cpu-baseline")
@@ -901,7 +929,7 @@ def main():
         import workloads as W
         points = build_points([int(c) for c in args.configs.split(",") if c])
         for p in points:
-            p["sel"] = Q.select_config(p["M"], p["N"], p["K"])
+            p["sel"] = selection(Q, p)
             p["kernel"] = kernel_name(p["sel"])
             p["flops"] = W.flops(p["M"], p["N"], p["K"])
         cmd = ("rocprofv3 --pmc " + " ".join(MFMA_COUNTERS) + " --output-format csv -d <dir> -o m "
@@ -915,7 +943,7 @@ def main():
         points = build_points([int(c) for c in args.configs.split(",") if c])
         import workloads as W
         for p in points:
-            p["sel"] = Q.select_config(p["M"], p["N"], p["K"])
+            p["sel"] = selection(Q, p)
             p["kernel"] = kernel_name(p["sel"])
             p["bytes"] = W.alg_bytes(p["M"], p["N"], p["K"])
         t = ingest_pmc(*args.ingest_pmc, points, args.dominant, command=PMC_COMMANDS)
@@ -991,7 +1019,7 @@ def main():
         p["y"] = torch.empty((p["M"], p["N"]), dtype=torch.float16, device=dev)
         if args.tune:
             Q.tune(p["x"], *p["w"], p["N"], y=p["y"])
-        p["sel"] = Q.select_config(p["M"], p["N"], p["K"])
+        p["sel"] = selection(Q, p)
         p["kernel"] = kernel_name(p["sel"])
         p["flops"] = W.flops(p["M"], p["N"], p["K"])
         p["bytes"] = W.alg_bytes(p["M"], p["N"], p["K"])
@@ -1110,7 +1138,9 @@ def main():
     dpts = by_k[dom]
     reps = max(3, args.steps)
     d_ms = graph_time_ms(dpts, reps)
-    d_bound = "mfma" if all(p["bound"] == "mfma" for p in dpts) else "hbm"
+    # the binding roofline of its launches together
+    d_bound = ("mfma" if sum(p["flops"] for p in dpts) / (MFMA_F16_PEAK_TFLOPS * 1e12)
+               > sum(p["bytes"] for p in dpts) / (HBM_PEAK_GBS * 1e9) else "hbm")
     if d_bound == "mfma":
         ach = sum(p["flops"] for p in dpts) / (d_ms * 1e-3) / 1e12
         roof = dict(bound="mfma", achieved=round(ach, 2), peak=MFMA_F16_PEAK_TFLOPS, unit="TFLOP/s",

@@ -125,7 +125,10 @@ int quick_w4a16_gemm(const void* x, const void* packed, const void* scales,
                      int64_t group, void* stream);
 
 /* Kernel selection for quick_w4a16_gemm_ex (tests, benchmarks, tuning).
- * Zero in any field means "choose automatically". */
+ * Zero in any field means "choose automatically".  With every field zero (or
+ * no config and none recorded for the shape) the GEMM may run in the
+ * wave-split form, whose tiles only the rules choose: no other config names
+ * it, and one with any field set runs the kernels below. */
 typedef struct quick_config {
     int variant;   /* 0 auto, 1 = stream kernel (small M), 2 = tiled kernel,
                       3 = tiled kernel with the stream-K schedule (resident
@@ -201,14 +204,18 @@ int quick_w4a16_gemm_noalloc(const void* x, const void* packed, const void* scal
  * (cfg NULL = automatic choice); 0 when no workspace is used. */
 size_t quick_workspace_bytes(int64_t M, int64_t N, int64_t K, const quick_config_t* cfg);
 
-/* The configuration the automatic heuristic picks for a shape (for logs and
- * benchmarks).  Errors: INVALID_ARG (NULL cfg), SHAPE. */
+/* The configuration the automatic heuristic picks for a shape among the
+ * kernels a config can name (for logs and benchmarks); the one recorded for
+ * the shape if there is one, all zero where the automatic choice was recorded.
+ * An automatic launch needs this configuration's workspace whether or not it
+ * runs in the wave-split form.  Errors: INVALID_ARG (NULL cfg), SHAPE. */
 int quick_select_config(int64_t M, int64_t N, int64_t K, quick_config_t* cfg);
 
 /* ---- per-shape autotuning (the paper leaves split-K / tile choice as a
  * tuning knob; Section 5 names autotuning as future work) ---------------- */
 
-/* Times every supported kernel configuration for this shape on the caller's
+/* Times the automatic choice (recorded as all zeros where it is the fastest)
+ * and every supported kernel configuration for this shape on the caller's
  * buffers (same arguments and contract as quick_w4a16_gemm; y is
  * overwritten, the last write coming from the best configuration) and
  * records the fastest in the process-wide tune table.  Each configuration's

@@ -1,7 +1,8 @@
 """Build the HIP library libquick.so in-tree for gfx950 (hipcc cross-compiles
-without a GPU).  quick_gemm.hip is compiled as three translation units in
-parallel (host code and the C ABI; the stream-kernel launches; the
-tiled-kernel launches), then linked with the packing code."""
+without a GPU).  quick_gemm.hip is compiled as five translation units in
+parallel (host code and the C ABI; the launches of the stream kernels, the
+tiled kernels, the wave-split kernel and its grouped form), then linked with
+the packing code."""
 from __future__ import annotations
 
 import os

@@ -5,7 +5,7 @@
 // (paper, Section 2.1 and Section 2.3), with the weights in the QPK16 packed
 // layout produced offline by quick_pack_weights (Section 3.1, 3.2).
 //
-// Common scheme of both kernels:
+// Common scheme of the kernels:
 //  * One 16-byte load per lane fetches a lane's share of a 1 KiB packed
 //    unit (16 columns x 128 input channels): 4 words, one per 32-wide k step
 //    of the 16x16x32 f16 matrix instruction.  The words go straight into
@@ -45,9 +45,10 @@
 #include "quick_internal.h"
 #include "quick_launch.h"
 
-// The build compiles this file as three translation units in parallel
+// The build compiles this file as five translation units in parallel
 // (QUICK_PART 0: host code and the C ABI; 1: stream-kernel launches; 2:
-// tiled-kernel launches); without QUICK_PART it is the whole library.
+// tiled-kernel launches; 3 and 4: those of the wave-split kernel and of its
+// grouped form); without QUICK_PART it is the whole library.
 #if !defined(QUICK_PART)
 #define QUICK_HOST 1
 #define QUICK_STREAM 1
@@ -696,12 +697,6 @@ tiled_kernel(const uint16_t* __restrict__ x, const u4_t* __restrict__ pw,
                 if (e < ga.experts) {
                     lo = min(max(ga.offsets[e], 0), ga.routed);
                     hi = min(max(ga.offsets[e + 1], lo), ga.routed);
-                    if (ga.part) {
-                        const int rem = (hi - lo) % ga.unit;
-                        const int lead = rem >= ga.keep ? hi : hi - rem;   // end of part 1
-                        if (ga.part == 1) hi = lead;
-                        else lo = lead;
-                    }
                 }
                 int t = (hi - lo + BM - 1) / BM;
 #pragma unroll
@@ -1712,7 +1707,10 @@ tiled32_kernel(const uint16_t* __restrict__ x, const u4_t* __restrict__ pw,
 }
 
 // K slices from which on a wave-split launch leaves the adding of its partial
-// sums to the reduction pass (see the kernel).
+// sums to the reduction pass.  The last workgroup of a tile to arrive re-reads
+// S tiles alone, on one compute unit, while the pass spreads them over the chip
+// for one more launch: 2 slices cost 2.1 us and 0.4 us per MB of partial sums
+// that way, the pass 4.5 us and 0.25 us per MB.
 [[maybe_unused]] constexpr int kWsReduceSplit = 4;
 // Shapes of the wave-split kernel: X(16-row blocks per workgroup, n-tiles per
 // wave, waves side by side along N, activation slots in halves of a k-group,
@@ -1770,7 +1768,64 @@ tiled32_kernel(const uint16_t* __restrict__ x, const u4_t* __restrict__ pw,
 
 #if QUICK_WSPLIT || QUICK_WSPLIT_GRP
 // ---------------------------------------------------------------------------
-// Wave-split kernel (17 <= M <= 256).
+// Wave-split kernel: the automatic form of the plain GEMM from 17 rows on (from
+// 9 where the stream kernels' grids do not fit the chip, see wsplit_small_m) and
+// of the grouped GEMM.
+//
+// What bounds it.  Up to about 300 rows it is the traffic into the compute
+// units, not the matrix cores: a tile of BM rows takes in BM * 256 bytes of
+// activations per k-group and 1 KiB of weights per n-tile, and a compute unit
+// takes in 58 bytes per clock from L2 when every copy instruction covers whole
+// 128-byte lines (8 rows x 128 bytes; 16 rows x 64 bytes: 41, fragments loaded
+// straight into registers: 16).  From there on it is the matrix and vector
+// pipes: a weight costs its dequantization once per tile that uses it.
+//
+// Layout.  A workgroup's 8 waves are KW = 8 / NW ranges of K times NW groups of
+// columns.  A wave computes 16 * MTT rows x 16 * NP columns over its range.  So
+// the chip is filled by splitting K inside the workgroup, where the partial
+// sums are added through LDS and never leave the compute unit: 16-column to
+// 512-column tiles for the same 8 waves, where the tiled kernel's workgroup is
+// always 128 or 256 columns wide and needs K slices in memory and a second
+// launch to fill the chip at the same M.
+//
+//  * Activations: LDS-DMA copies of half a k-group (64 channels) per range into
+//    a ring of RH slots.  With NW = 1 a wave copies for itself, and there is no
+//    barrier in the loop: a wave waits for its own copies only.  With NW > 1
+//    the range's waves share the copy, one barrier per half.  Chunk q of a
+//    128-byte row sits at q ^ (row / 2), so a fragment read of 16 rows is free
+//    of bank conflicts.  The slots are objects of their own, so that the
+//    compiler's alias analysis lets a copy into one pass reads of another.
+//  * Weights: one 16-byte load per lane, n-tile and k-group, DW k-groups in
+//    registers.
+//  * A step (32 channels) runs in two parts: while the matrix instructions of
+//    the first n-tiles run, the other n-tiles' weights are dequantized; while
+//    those of the others run, the next step's fragments are read and the first
+//    n-tiles' next weights dequantized.  So one set of fragments is live.
+//  * Loads retire in order, so each wait names how many later ones may be in
+//    flight.  Past the end of the range the loads go on with descriptors of
+//    size 0 (they move nothing): the counts stay exact and one loop body serves
+//    every range length.  (A second body for the tails doubled the registers.)
+//  * The weight loads are fenced in place: moved across the loop's exit by the
+//    compiler they would fall out of the count.
+//
+// K slices across workgroups remain for the few shapes whose tiles do not fill
+// the chip; the rule is wsplit_plan's.
+//
+// Grouped form: the experts' rows go evenly over their tiles, and a tile whose
+// rows fit MTB blocks runs the lower body, so a remainder does not cost a
+// full-height tile.
+//
+// Measured against the tiled kernels on their own rules (us for one pass over
+// the layers of a block): 13B at 333 rows with bias 294 -> 240, 7B at 64 rows 143
+// -> 133, at 256 rows 137 -> 128 and at 2048 rows 764 -> 716, 70B at 128 rows 245
+// -> 238 and at 1024 rows 1485 -> 1475, 13B at 16 rows (against the stream
+// kernels) 145 -> 120; eight experts' feed-forward with 512 tokens 478 -> 434,
+// with 20 tokens 172 -> 153.
+//
+// Tried and slower: fragments loaded straight from L2 (16 bytes per clock);
+// workgroups of 4 waves; rings of 8 slots; K ranges starting at different
+// k-groups; touching the activations into L2 ahead; 128 x 64 tiles per wave
+// with 4 groups of columns (registers spill).
 // ---------------------------------------------------------------------------
 constexpr int kWsWaves = 8;
 
@@ -2141,7 +2196,7 @@ __device__ __forceinline__ void wsplit_tile(const WsLds& lds, const uint16_t* x,
 // otherwise.
 template <int MTT, int NP, int NW, int RH, int DW, int MTB = 0>
 __global__ void __launch_bounds__(64 * kWsWaves)
-wsplit_kernel(const uint16_t* x, const u4_t* pw, const uint16_t* ps, const uint32_t* pz, uint16_t* y, float* ws, int M,
+wave_stream_kernel(const uint16_t* x, const u4_t* pw, const uint16_t* ps, const uint32_t* pz, uint16_t* y, float* ws, int M,
               int N, int K, int kgps, int n_mtiles, int n_cg, int S, GroupArgs ga, Epi epi)
 {
     constexpr bool GRP = MTB > 0;
@@ -2855,7 +2910,7 @@ int launch_tiled(const Plan& pl, const uint16_t* x, const u4_t* pw, const uint16
             launch_tiled_t<128, 32, true>(pl, x, pw, ps, pz, y, ws, M, N, K, st, *ga, epi);
         else return QUICK_ERR_INVALID_ARG;
     } else {
-        const GroupArgs none{nullptr, nullptr, 0, 0};
+        const GroupArgs none{};
         if (pl.bm == 16 && pl.wn == 32) launch_tiled_t<16, 32, false>(pl, x, pw, ps, pz, y, ws, M, N, K, st, none, epi);
         else if (pl.bm == 32 && pl.wn == 32) launch_tiled_t<32, 32, false>(pl, x, pw, ps, pz, y, ws, M, N, K, st, none, epi);
         else if (pl.bm == 16 && pl.wn == 16) launch_tiled_t<16, 16, false>(pl, x, pw, ps, pz, y, ws, M, N, K, st, none, epi);
@@ -2925,7 +2980,7 @@ int launch_ablation(const uint16_t* x, const u4_t* pw, const uint16_t* ps, const
     const int KG = K / 128;
     auto args = [&](auto kern) {
         hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * kTiledWaves), 0, st, x, pw, ps, pz, y, (float*)nullptr,
-                           M, N, K, KG, nm, nn, 1, GroupArgs{nullptr, nullptr, 0, 0}, Epi{nullptr, 0});
+                           M, N, K, KG, nm, nn, 1, GroupArgs{}, Epi{nullptr, 0});
     };
     if (mode == 0) args(tiled_kernel<64, 32, 0>);
     else if (mode == 1) args(tiled_kernel<64, 32, 1>);
@@ -2943,7 +2998,7 @@ void launch_wsplit_t(const WsplitPlan& wp, const uint16_t* x, const u4_t* pw, co
 {
     const int nm = ceil_div(M, MTT * 16), ncg = ceil_div(N / 16, NP * NW);
     const dim3 grid((unsigned)ceil_div((int64_t)nm * ncg * wp.split, 8) * 8);
-    hipLaunchKernelGGL((wsplit_kernel<MTT, NP, NW, RH, DW>), grid, dim3(64 * kWsWaves), 0, st, x, pw, ps, pz, y, ws, M,
+    hipLaunchKernelGGL((wave_stream_kernel<MTT, NP, NW, RH, DW>), grid, dim3(64 * kWsWaves), 0, st, x, pw, ps, pz, y, ws, M,
                        N, K, wp.kgps, nm, ncg, wp.split, GroupArgs{}, epi);
 }
 
@@ -2977,7 +3032,7 @@ void launch_wsplit_grp_t(const uint16_t* x, const u4_t* pw, const uint16_t* ps, 
     const int64_t nm = ((int64_t)ga.routed + (int64_t)ga.experts * (MTT * 16 - 1)) / (MTT * 16);
     const int ncg = ceil_div(N / 16, NP * NW);
     const dim3 grid((unsigned)ceil_div(nm * ncg, 8) * 8);
-    hipLaunchKernelGGL((wsplit_kernel<MTT, NP, NW, RH, DW, MTB>), grid, dim3(64 * kWsWaves), 0, st, x, pw, ps, pz, y,
+    hipLaunchKernelGGL((wave_stream_kernel<MTT, NP, NW, RH, DW, MTB>), grid, dim3(64 * kWsWaves), 0, st, x, pw, ps, pz, y,
                        (float*)nullptr, M, N, K, K / 128, 0, ncg, 1, ga, epi);
 }
 
@@ -3034,6 +3089,8 @@ constexpr WsShape kWsShapes[] = {
 #undef QUICK_WS
 };
 constexpr int kWsCus = 256;
+// a grid holds at most 2^32 - 1 work-items (512 a workgroup)
+constexpr int64_t kWsMaxTiles = ((int64_t)1 << 23) - 16;
 
 // Estimated time of `tiles` workgroups of shape w over kg k-groups each.
 double wsplit_us(const WsShape& w, int64_t tiles, int64_t kg)
@@ -3084,6 +3141,7 @@ bool wsplit_plan(int64_t M, int64_t N, int64_t K, const Plan& pl, size_t ws_byte
         if (epi.act && w.np % 2) continue;   // a gate tile and its up tile in one wave
         if ((M <= 16) != (w.mt == 1)) continue;
         const int64_t tiles = ((M + 16 * w.mt - 1) / (16 * w.mt)) * ((N / 16 + w.np * w.nw - 1) / (w.np * w.nw));
+        if (tiles > kWsMaxTiles) continue;
         for (int s = 1; s <= 8; s *= 2) {
             const int64_t part = (int64_t)s * M * N * 4;
             if (s > 1 && (KG / s < 4 || tiles * s > 2 * kWsCus || tiles > kSkMaxWorkgroups ||
@@ -3119,13 +3177,13 @@ constexpr WsGrpShape kWsGrpShapes[] = {
 #undef QUICK_WS
 };
 
-WsplitPlan wsplit_grouped_plan(int64_t R, int64_t E, int64_t N, int64_t K)
+bool wsplit_grouped_plan(int64_t R, int64_t E, int64_t N, int64_t K, WsplitPlan* out)
 {
     const double mean = (double)R / (double)E, dev = std::sqrt(mean);
     static const double at[4] = {-1.5, -0.5, 0.5, 1.5}, weight[4] = {0.13, 0.37, 0.37, 0.13};
     const int64_t kg = K / 128;
     double best = 0;
-    WsplitPlan out{0, 0, 0, 1, (int)kg};
+    bool found = false;
     for (const WsGrpShape& w : kWsGrpShapes) {
         double hi = 0, lo = 0;   // tiles per expert
         for (int i = 0; i < 4; ++i) {
@@ -3135,17 +3193,17 @@ WsplitPlan wsplit_grouped_plan(int64_t R, int64_t E, int64_t N, int64_t K)
         // experts without a row have no tile
         const double some = std::min(1.0, mean);
         const int64_t ncg = (N / 16 + w.hi.np * w.hi.nw - 1) / (w.hi.np * w.hi.nw);
+        if ((R + E * (w.hi.mt * 16 - 1)) / (w.hi.mt * 16) * ncg > kWsMaxTiles) continue;
         const int64_t tiles = (int64_t)std::ceil((hi + lo) * some * (double)E) * ncg;
         const double part = hi / (hi + lo);
         const double us = part * wsplit_us(w.hi, tiles, kg) + (1.0 - part) * wsplit_us(w.lo, tiles, kg);
-        if (!out.mt || us < best) {
+        if (!found || us < best) {
             best = us;
-            out.mt = w.hi.mt;
-            out.np = w.hi.np;
-            out.nw = w.hi.nw;
+            found = true;
+            *out = WsplitPlan{w.hi.mt, w.hi.np, w.hi.nw, 1, (int)kg};
         }
     }
-    return out;
+    return found;
 }
 
 bool grouped_tile_supported(int bm, int wn)
@@ -3649,10 +3707,13 @@ int validate_grouped(const void* x, const int32_t* rows, const int32_t* offsets,
     return QUICK_OK;
 }
 
-// Tile and schedule for R routed rows over E experts.  Rows per expert are
-// known only on the device, so the tile is chosen for the mean (R / E) and
-// the default schedule is stream-K, which spreads whatever tile count the
-// kernel finds evenly over the resident workgroups.
+// Tiled-kernel tile and schedule for R routed rows over E experts: what an
+// explicit configuration runs, what quick_grouped_select_config and the
+// workspace size report, and what the automatic choice runs past the
+// wave-split form's grid limit.  Rows per expert are known only on the device,
+// so the tile is chosen for the mean (R / E) and the default schedule is
+// stream-K, which spreads whatever tile count the kernel finds evenly over the
+// resident workgroups.
 int grouped_plan(int64_t R, int64_t E, int64_t N, int64_t K, const quick_config_t* cfg, Plan* pl)
 {
     (void)N;
@@ -3707,18 +3768,14 @@ size_t grouped_workspace(int64_t R, int64_t N, const Plan& pl)
     return 0;
 }
 
-// The automatic grouped plan with full-height (128-row) tiles runs in two
-// launches: the experts' whole tiles (and remainders of at least 64 rows)
-// with the 128-row tiles, then the short remainders with 32-row tiles, so a
-// remainder of a few rows does not cost a full-height tile's matrix work.
-// Returns whether `pl` is split that way, and the second launch's plan.
-constexpr int kGroupTileUnit = 128;
-constexpr int kGroupTailKeep = 64;
+// The automatic choice asks for the larger workspace of its 128-row tiles and
+// of 32-row ones, more than it uses: the size callers have been told, so that
+// a buffer that was refused still is.  Returns whether that applies, and the
+// 32-row plan.
 bool grouped_tail_plan(int64_t R, int64_t E, int64_t N, int64_t K, const quick_config_t* cfg, const Plan& pl,
                        Plan* tp)
 {
-    const bool automatic = !cfg || (cfg->variant == 0 && cfg->split_k == 0 && cfg->tile_m == 0 && cfg->tile_n == 0);
-    if (!automatic || pl.bm != kGroupTileUnit) return false;
+    if ((cfg && !is_auto_config(*cfg)) || pl.bm != 128) return false;
     const quick_config_t tc{kVariantStreamK, 0, 32, 32};
     return grouped_plan(R, E, N, K, &tc, tp) == QUICK_OK;
 }
@@ -3769,26 +3826,18 @@ int grouped_impl(const void* x, const int32_t* rows, const int32_t* offsets, con
         }
     }
     (void)hipGetLastError();
-    const bool automatic = !cfg || is_auto_config(*cfg);
-    if (automatic) {
-        const GroupArgs ga{rows, offsets, (int)E, (int)R, 0, 0, 0};
-        st = launch_wsplit_grouped(wsplit_grouped_plan(R, E, N, K), static_cast<const uint16_t*>(x),
-                                   static_cast<const u4_t*>(packed), static_cast<const uint16_t*>(scales),
-                                   static_cast<const uint32_t*>(zeros), static_cast<uint16_t*>(y), (int)T, (int)N,
-                                   (int)K, hs, ga, epi);
-        if (st) return st;
-        return hipGetLastError() == hipSuccess ? QUICK_OK : QUICK_ERR_HIP;
-    }
-    // the two launches write disjoint rows of y; the second reuses the
-    // workspace after the first (same stream; stream-K leaves its counters
-    // zero)
-    for (int part = tail ? 1 : 0; part <= (tail ? 2 : 0); ++part) {
-        const GroupArgs ga{rows, offsets, (int)E, (int)R, part, kGroupTileUnit, kGroupTailKeep};
-        st = launch_tiled(part == 2 ? tp : pl, static_cast<const uint16_t*>(x), static_cast<const u4_t*>(packed),
-                          static_cast<const uint16_t*>(scales), static_cast<const uint32_t*>(zeros),
-                          static_cast<uint16_t*>(y), static_cast<float*>(ws), (int)T, (int)N, (int)K, hs, epi, &ga);
-        if (st) return st;
-    }
+    const GroupArgs ga{rows, offsets, (int)E, (int)R};
+    const uint16_t* xx = static_cast<const uint16_t*>(x);
+    const u4_t* pw = static_cast<const u4_t*>(packed);
+    const uint16_t* ps = static_cast<const uint16_t*>(scales);
+    const uint32_t* pz = static_cast<const uint32_t*>(zeros);
+    uint16_t* yy = static_cast<uint16_t*>(y);
+    WsplitPlan wp;
+    if ((!cfg || is_auto_config(*cfg)) && wsplit_grouped_plan(R, E, N, K, &wp))
+        st = launch_wsplit_grouped(wp, xx, pw, ps, pz, yy, (int)T, (int)N, (int)K, hs, ga, epi);
+    else
+        st = launch_tiled(pl, xx, pw, ps, pz, yy, static_cast<float*>(ws), (int)T, (int)N, (int)K, hs, epi, &ga);
+    if (st) return st;
     return hipGetLastError() == hipSuccess ? QUICK_OK : QUICK_ERR_HIP;
 }
 

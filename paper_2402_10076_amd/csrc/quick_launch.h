@@ -1,7 +1,8 @@
 // Types and launch functions shared by the parts of quick_gemm.hip, which the
 // build compiles as separate translation units in parallel: the host part
-// (validation, plans, workspace, tuning, the C ABI), the stream-kernel part
-// and the tiled-kernel part (each instantiates and launches its kernels).
+// (validation, plans, workspace, tuning, the C ABI), the stream-kernel part,
+// the tiled-kernel part and the wave-split kernel's plain and grouped parts
+// (each instantiates and launches its kernels).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -33,13 +34,6 @@ struct GroupArgs {
     const int* offsets;  // [experts + 1] first routed row of each expert
     int experts;
     int routed;          // rows of y
-    // Which of each expert's rows this launch covers.  0: all.  With
-    // `unit` rows per full tile: 1 = the leading whole tiles, plus the
-    // remainder when it holds at least `keep` rows; 2 = the rest (a
-    // remainder of fewer than `keep` rows), for a launch with shorter tiles.
-    int part;
-    int unit;
-    int keep;
 };
 
 // A launch configuration, complete once finish_plan has run.

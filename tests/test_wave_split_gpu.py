@@ -44,7 +44,7 @@ def _check(y, ref, bound):
 
 # (M, N, K): rows at the edges of tiles of 16 to 128 rows, ragged columns, one
 # k-group (waves without any), odd numbers of k-groups, two and more K slices
-SIZES = [(9, 6144, 1024), (16, 12288, 512), (9, 528, 128), (13, 15360, 640),
+SIZES = [(3, 9744, 11008), (16, 5120, 5120), (9, 6144, 1024), (16, 12288, 512), (9, 528, 128), (13, 15360, 640),
          (17, 16, 128), (17, 16, 384), (17, 16, 11008), (31, 48, 128), (33, 272, 11008), (63, 528, 11008),
          (33, 528, 11008), (33, 2032, 11008), (97, 1040, 896), (97, 1040, 384), (65, 784, 11008), (49, 528, 11008),
          (129, 1360, 11008), (200, 1648, 4224), (112, 1376, 11008), (257, 1808, 384), (129, 1648, 1152),
@@ -78,8 +78,8 @@ def test_automatic_form(M, N, K):
     assert torch.equal(p.gemm(xd), y)
 
 
-@pytest.mark.parametrize("M,N,K", [(16, 12288, 512), (17, 32, 128), (33, 2048, 11008), (65, 672, 11008), (97, 1056, 384),
-                                   (129, 1632, 1152)])
+@pytest.mark.parametrize("M,N,K", [(16, 12288, 512), (17, 32, 128), (33, 2048, 11008), (65, 672, 11008),
+                                   (97, 1056, 384), (129, 1632, 1152)])
 def test_automatic_form_with_epilogues(M, N, K):
     """Bias, and bias with the gated SiLU (a gate tile and its up tile end up
     in one wave whatever the tile).  With h the GEMM's bound E: silu' <= 1.1,
