@@ -1717,7 +1717,9 @@ tiled32_kernel(const uint16_t* __restrict__ x, const u4_t* __restrict__ pw,
 // weight slots in k-groups, us per launch, us per further round of workgroups,
 // us per k-group).  Two activation slots where the ranges' copies are private
 // and small (16 x 5120 x 5120 8.9 -> 8.4 us against four: more workgroups share a
-// compute unit), four where waves share them, to cover the barriers.
+// compute unit; (2, 3, 1) won at 64 x 12288 x 4096, 20.8 -> 17.8, and lost at 32
+// rows, 12.2 -> 12.6, and keeps four), four where waves share them, to cover the
+// barriers (two at 5 blocks and 2 groups of columns, for the LDS).
 #define QUICK_WSPLIT_SHAPES(X) \
     X(1, 2, 1, 2, 2, 3.0f, 0.6f, 0.129f) \
     X(1, 3, 1, 2, 2, 3.0f, 0.6f, 0.161f) \
