@@ -211,6 +211,25 @@ size_t quick_workspace_bytes(int64_t M, int64_t N, int64_t K, const quick_config
  * runs in the wave-split form.  Errors: INVALID_ARG (NULL cfg), SHAPE. */
 int quick_select_config(int64_t M, int64_t N, int64_t K, quick_config_t* cfg);
 
+/* What a call launches (for logs and benchmarks). */
+typedef struct quick_launch {
+    int variant;   /* 0 = wave-split form, else as in quick_config_t          */
+    int split_k;   /* wave-split: K slices across workgroups, else as in
+                      quick_config_t                                         */
+    int tile_m;    /* rows per workgroup (0: stream kernels, all M)           */
+    int tile_n;    /* wave-split: columns per workgroup, else as in
+                      quick_config_t                                         */
+    int k_ranges;  /* wave-split: ranges of K inside a workgroup, else 0      */
+    int launches;  /* kernels enqueued (2: with the pass that adds up the
+                      partial sums of split_k slices; M == 0: 0)             */
+} quick_launch_t;
+
+/* The launch of quick_w4a16_gemm_ex for this shape and cfg (NULL = automatic
+ * choice, including a recorded one); with `gated` nonzero, of
+ * quick_w4a16_gemm_fused with QUICK_ACT_SILU_GATE.  Host only.
+ * Errors: as those calls for the shape and the cfg, INVALID_ARG (NULL out). */
+int quick_launch_plan(int64_t M, int64_t N, int64_t K, const quick_config_t* cfg, int gated, quick_launch_t* out);
+
 /* ---- per-shape autotuning (the paper leaves split-K / tile choice as a
  * tuning knob; Section 5 names autotuning as future work) ---------------- */
 

@@ -89,6 +89,12 @@ size_t quick_grouped_workspace_bytes(int64_t R, int64_t E, int64_t N, int64_t K,
  * Errors: INVALID_ARG (NULL cfg), SHAPE. */
 int quick_grouped_select_config(int64_t R, int64_t E, int64_t N, int64_t K, quick_config_t* cfg);
 
+/* The launch of quick_w4a16_grouped_gemm_ex for these sizes and cfg (NULL =
+ * automatic choice); tile_m is that of the tallest tiles.  Host only.
+ * Errors: SHAPE, INVALID_ARG (NULL out, cfg). */
+int quick_grouped_launch_plan(int64_t R, int64_t E, int64_t N, int64_t K, const quick_config_t* cfg,
+                              quick_launch_t* out);
+
 #ifdef __cplusplus
 }
 #endif

@@ -11,7 +11,8 @@ Entry points mirror include/quick.h:
 * ``pack_weights(q, z, s_bits, group=128)`` -> (packed, scales, zeros) numpy
 * ``unpack_weights(packed, scales, zeros, K, N, group=128)``
 * ``w4a16_gemm(x, packed, scales, zeros, N, y=None, group=128, ...)``
-* ``select_config(M, N, K)``, ``workspace_bytes(M, N, K, cfg=None)``
+* ``select_config(M, N, K)``, ``workspace_bytes(M, N, K, cfg=None)``,
+  ``launch_plan(M, N, K, cfg=None, gated=False)``
 * ``grouped_gemm(x, offsets, packed, scales, zeros, N, rows=None, ...)``
   (include/quick_grouped.h), ``pack_experts(experts)``
 * ``gemm_fused`` / ``grouped_gemm_fused`` with a bias and the gated SiLU
@@ -78,6 +79,12 @@ class QuickConfig(ctypes.Structure):
         return {f: getattr(self, f) for f, _ in self._fields_}
 
 
+class QuickLaunch(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int) for n in ("variant", "split_k", "tile_m", "tile_n", "k_ranges", "launches")]
+
+    as_dict = QuickConfig.as_dict
+
+
 class QuickEpilogue(ctypes.Structure):
     _fields_ = [("bias", ctypes.c_void_p), ("activation", ctypes.c_int)]
 
@@ -120,6 +127,8 @@ def lib():
             L.quick_workspace_bytes.restype = SZ
             L.quick_select_config.argtypes = [I64, I64, I64, ctypes.POINTER(QuickConfig)]
             L.quick_select_config.restype = I
+            L.quick_launch_plan.argtypes = [I64, I64, I64, ctypes.POINTER(QuickConfig), I, ctypes.POINTER(QuickLaunch)]
+            L.quick_launch_plan.restype = I
             L.quick_tune.argtypes = [P, P, P, P, P, I64, I64, I64, I64, P, ctypes.POINTER(QuickConfig)]
             L.quick_tune.restype = I
             L.quick_tune_table_save.argtypes = [ctypes.c_char_p]
@@ -141,6 +150,9 @@ def lib():
             L.quick_grouped_workspace_bytes.restype = SZ
             L.quick_grouped_select_config.argtypes = [I64, I64, I64, I64, ctypes.POINTER(QuickConfig)]
             L.quick_grouped_select_config.restype = I
+            L.quick_grouped_launch_plan.argtypes = [I64, I64, I64, I64, ctypes.POINTER(QuickConfig),
+                                                    ctypes.POINTER(QuickLaunch)]
+            L.quick_grouped_launch_plan.restype = I
             EP = ctypes.POINTER(QuickEpilogue)
             L.quick_w4a16_gemm_fused.argtypes = [P, P, P, P, P, I64, I64, I64, I64, P, EP,
                                                  ctypes.POINTER(QuickConfig), P, SZ]
@@ -231,6 +243,14 @@ def select_config(M: int, N: int, K: int) -> dict:
     c = QuickConfig()
     _check(lib().quick_select_config(M, N, K, ctypes.byref(c)), "quick_select_config")
     return c.as_dict()
+
+
+def launch_plan(M: int, N: int, K: int, cfg: QuickConfig | None = None, gated: bool = False) -> dict:
+    """What w4a16_gemm (with ``gated``, gemm_fused with the gated SiLU) launches for these sizes."""
+    p = QuickLaunch()
+    _check(lib().quick_launch_plan(M, N, K, ctypes.byref(cfg) if cfg is not None else None, int(gated),
+                                   ctypes.byref(p)), "quick_launch_plan")
+    return p.as_dict()
 
 
 def workspace_bytes(M: int, N: int, K: int, cfg: QuickConfig | None = None) -> int:
@@ -420,6 +440,14 @@ def grouped_select_config(R: int, E: int, N: int, K: int) -> dict:
     return c.as_dict()
 
 
+def grouped_launch_plan(R: int, E: int, N: int, K: int, cfg: QuickConfig | None = None) -> dict:
+    """What grouped_gemm launches for R routed rows over E experts."""
+    p = QuickLaunch()
+    _check(lib().quick_grouped_launch_plan(R, E, N, K, ctypes.byref(cfg) if cfg is not None else None,
+                                           ctypes.byref(p)), "quick_grouped_launch_plan")
+    return p.as_dict()
+
+
 def grouped_workspace_bytes(R: int, E: int, N: int, K: int, cfg: QuickConfig | None = None) -> int:
     return int(lib().quick_grouped_workspace_bytes(R, E, N, K, ctypes.byref(cfg) if cfg is not None else None))
 
@@ -568,9 +596,10 @@ EXPORTED = (
     "quick_status_string", "quick_pack_format_version", "quick_packed_sizes", "quick_pack_weights",
     "quick_unpack_weights", "quick_w4a16_gemm", "quick_w4a16_gemm_ex", "quick_w4a16_gemm_noalloc",
     "quick_workspace_bytes",
-    "quick_select_config", "quick_tune", "quick_tune_table_save", "quick_tune_table_load",
+    "quick_select_config", "quick_launch_plan", "quick_tune", "quick_tune_table_save", "quick_tune_table_load",
     "quick_tune_table_size", "quick_tune_table_clear", "quick_ablation_gemm",
     "quick_w4a16_grouped_gemm", "quick_w4a16_grouped_gemm_ex", "quick_grouped_workspace_bytes",
-    "quick_grouped_select_config", "quick_w4a16_gemm_fused", "quick_w4a16_grouped_gemm_fused",
+    "quick_grouped_select_config", "quick_grouped_launch_plan", "quick_w4a16_gemm_fused",
+    "quick_w4a16_grouped_gemm_fused",
     "quick_fused_workspace_bytes", "quick_grouped_fused_workspace_bytes", "quick_interleave_gate_up",
 )

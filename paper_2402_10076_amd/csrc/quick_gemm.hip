@@ -3221,10 +3221,8 @@ bool grouped_tile_supported(int bm, int wn)
 
 bool aligned(const void* p, uintptr_t a) { return ((uintptr_t)p % a) == 0; }
 
-int validate(const void* x, const void* packed, const void* scales, const void* zeros, void* y,
-             int64_t M, int64_t N, int64_t K, int64_t group)
+int check_shape(int64_t M, int64_t N, int64_t K)
 {
-    if (group != quick::kGroup) return QUICK_ERR_UNSUPPORTED;
     if (M < 0 || N <= 0 || K <= 0 || K % 128 != 0 || N % 16 != 0) return QUICK_ERR_SHAPE;
     // 32-bit buffer offsets and index arithmetic inside the kernels: packed
     // weights (K*N/2 bytes) and activations (2*M*K bytes) below 4 GiB, the
@@ -3232,6 +3230,15 @@ int validate(const void* x, const void* packed, const void* scales, const void* 
     if (K * N / 2 >= ((int64_t)1 << 32) || M * K >= ((int64_t)1 << 31) || M * N >= ((int64_t)1 << 31) ||
         M > (1 << 24))
         return QUICK_ERR_SHAPE;
+    return QUICK_OK;
+}
+
+int validate(const void* x, const void* packed, const void* scales, const void* zeros, void* y,
+             int64_t M, int64_t N, int64_t K, int64_t group)
+{
+    if (group != quick::kGroup) return QUICK_ERR_UNSUPPORTED;
+    const int st = check_shape(M, N, K);
+    if (st) return st;
     if (M == 0) return QUICK_OK;
     if (!x || !packed || !scales || !zeros || !y) return QUICK_ERR_INVALID_ARG;
     if (!aligned(x, 16) || !aligned(packed, 16) || !aligned(scales, 2) || !aligned(zeros, 4) ||
@@ -3260,6 +3267,27 @@ int epilogue_plan(const Epi& epi, const quick_config_t* cfg, Plan* pl)
     return QUICK_OK;
 }
 
+// What a plain GEMM launches: the plan among the kernels a configuration can
+// name, its workspace, and the wave-split launch where that runs instead.
+struct Launch {
+    Plan pl;
+    size_t need;
+    bool wave;
+    WsplitPlan wp;
+};
+
+int plan_launch(int64_t M, int64_t N, int64_t K, const quick_config_t* cfg, const Epi& epi, Launch* out)
+{
+    int st = make_plan(M, N, K, cfg, &out->pl);
+    if (st) return st;
+    st = epilogue_plan(epi, cfg, &out->pl);
+    if (st || M == 0) return st;
+    finish_plan(M, N, K, &out->pl);
+    out->need = plan_workspace(M, N, out->pl);
+    out->wave = is_automatic(M, N, K, cfg) && wsplit_plan(M, N, K, out->pl, out->need, epi, &out->wp);
+    return QUICK_OK;
+}
+
 int gemm_impl(const void* x, const void* packed, const void* scales, const void* zeros, void* y,
               int64_t M, int64_t N, int64_t K, int64_t group, void* stream, const quick_config_t* cfg,
               void* workspace, size_t workspace_bytes, const Epi& epi = Epi{nullptr, 0})
@@ -3269,17 +3297,12 @@ int gemm_impl(const void* x, const void* packed, const void* scales, const void*
     if (epi.act < 0 || epi.act > 1) return QUICK_ERR_INVALID_ARG;
     if (epi.act && N % 32 != 0) return QUICK_ERR_SHAPE;
     if (M && epi.bias && !aligned(epi.bias, 8)) return QUICK_ERR_ALIGNMENT;
-    Plan pl;
-    st = make_plan(M, N, K, cfg, &pl);
-    if (st) return st;
-    st = epilogue_plan(epi, cfg, &pl);
-    if (st) return st;
-    if (M == 0) return QUICK_OK;
-    finish_plan(M, N, K, &pl);
+    Launch la;
+    st = plan_launch(M, N, K, cfg, epi, &la);
+    if (st || M == 0) return st;
+    const Plan& pl = la.pl;
+    const size_t need = la.need;
     hipStream_t hs = (hipStream_t)stream;
-    const size_t need = plan_workspace(M, N, pl);
-    WsplitPlan wp;
-    const bool wave = is_automatic(M, N, K, cfg) && wsplit_plan(M, N, K, pl, need, epi, &wp);
     void* ws = nullptr;
     if (need) {
         if (workspace) {
@@ -3297,8 +3320,8 @@ int gemm_impl(const void* x, const void* packed, const void* scales, const void*
     const uint32_t* pz = static_cast<const uint32_t*>(zeros);
     uint16_t* yy = static_cast<uint16_t*>(y);
     (void)hipGetLastError();  // clear a stale error so the check below is ours
-    if (wave)
-        st = launch_wsplit(wp, xx, pw, ps, pz, yy, static_cast<float*>(ws), (int)M, (int)N, (int)K, hs, epi);
+    if (la.wave)
+        st = launch_wsplit(la.wp, xx, pw, ps, pz, yy, static_cast<float*>(ws), (int)M, (int)N, (int)K, hs, epi);
     else if (pl.variant == kVariantStream)
         st = launch_stream(pl, xx, pw, ps, pz, yy, (int)M, (int)N, (int)K, hs, epi);
     else if (pl.variant == kVariantKStream)
@@ -3417,6 +3440,35 @@ extern "C" int quick_select_config(int64_t M, int64_t N, int64_t K, quick_config
     *cfg = quick_config_t{pl.variant, pl.split, is_tiled(pl.variant) ? pl.bm : 0, pl.wn};
     quick_config_t tuned;
     if (tuned_config(M, N, K, &tuned) && is_auto_config(tuned)) *cfg = tuned;   // tuned to the rules' choice
+    return QUICK_OK;
+}
+
+namespace {
+
+quick_launch_t describe(const Plan& pl)
+{
+    const bool pass = (pl.variant == kVariantTiled || pl.variant == kVariantTiled32) && pl.split > 1;
+    return quick_launch_t{pl.variant, pl.split, is_tiled(pl.variant) ? pl.bm : 0, pl.wn, 0, pass ? 2 : 1};
+}
+
+quick_launch_t describe(const WsplitPlan& wp)
+{
+    return quick_launch_t{0, wp.split, wp.mt * 16, wp.np * wp.nw * 16, 8 / wp.nw, wp.split >= kWsReduceSplit ? 2 : 1};
+}
+
+}  // namespace
+
+extern "C" int quick_launch_plan(int64_t M, int64_t N, int64_t K, const quick_config_t* cfg, int gated,
+                                 quick_launch_t* out)
+{
+    if (!out) return QUICK_ERR_INVALID_ARG;
+    int st = check_shape(M, N, K);
+    if (st) return st;
+    if (gated && N % 32 != 0) return QUICK_ERR_SHAPE;
+    Launch la;
+    st = plan_launch(M, N, K, cfg, Epi{nullptr, gated ? 1 : 0}, &la);
+    if (st) return st;
+    *out = M == 0 ? quick_launch_t{} : la.wave ? describe(la.wp) : describe(la.pl);
     return QUICK_OK;
 }
 
@@ -3802,6 +3854,12 @@ int grouped_epilogue_plan(const Epi& epi, const quick_config_t* cfg, Plan* pl)
     return QUICK_OK;
 }
 
+// Whether the grouped GEMM runs in the wave-split form, and its launch.
+bool grouped_wave(int64_t R, int64_t E, int64_t N, int64_t K, const quick_config_t* cfg, WsplitPlan* wp)
+{
+    return (!cfg || is_auto_config(*cfg)) && wsplit_grouped_plan(R, E, N, K, wp);
+}
+
 int grouped_impl(const void* x, const int32_t* rows, const int32_t* offsets, const void* packed,
                  const void* scales, const void* zeros, void* y, int64_t T, int64_t R, int64_t E, int64_t N,
                  int64_t K, int64_t group, void* stream, const quick_config_t* cfg, void* workspace,
@@ -3841,7 +3899,7 @@ int grouped_impl(const void* x, const int32_t* rows, const int32_t* offsets, con
     const uint32_t* pz = static_cast<const uint32_t*>(zeros);
     uint16_t* yy = static_cast<uint16_t*>(y);
     WsplitPlan wp;
-    if ((!cfg || is_auto_config(*cfg)) && wsplit_grouped_plan(R, E, N, K, &wp))
+    if (grouped_wave(R, E, N, K, cfg, &wp))
         st = launch_wsplit_grouped(wp, xx, pw, ps, pz, yy, (int)T, (int)N, (int)K, hs, ga, epi);
     else
         st = launch_tiled(pl, xx, pw, ps, pz, yy, static_cast<float*>(ws), (int)T, (int)N, (int)K, hs, epi, &ga);
@@ -3892,6 +3950,21 @@ extern "C" int quick_grouped_select_config(int64_t R, int64_t E, int64_t N, int6
     cfg->split_k = pl.split;
     cfg->tile_m = pl.bm;
     cfg->tile_n = pl.wn;
+    return QUICK_OK;
+}
+
+extern "C" int quick_grouped_launch_plan(int64_t R, int64_t E, int64_t N, int64_t K, const quick_config_t* cfg,
+                                         quick_launch_t* out)
+{
+    if (!out) return QUICK_ERR_INVALID_ARG;
+    if (R < 0 || E < 1 || E > kMaxExperts || N <= 0 || K <= 0 || K % 128 != 0 || N % 16 != 0 ||
+        K * N / 2 >= ((int64_t)1 << 32) || R * N >= ((int64_t)1 << 31) || R > (1 << 24))
+        return QUICK_ERR_SHAPE;
+    Plan pl;
+    const int st = grouped_plan(R, E, N, K, cfg, &pl);
+    if (st) return st;
+    WsplitPlan wp;
+    *out = R == 0 ? quick_launch_t{} : grouped_wave(R, E, N, K, cfg, &wp) ? describe(wp) : describe(pl);
     return QUICK_OK;
 }
 

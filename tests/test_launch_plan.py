@@ -1,0 +1,71 @@
+"""What a call launches, through the library's own planner on the host
+(quick_launch_plan, quick_grouped_launch_plan): which sizes run in the
+wave-split form and which in a kernel that a configuration names."""
+import ctypes
+
+import pytest
+
+import paper_2402_10076_amd as Q
+
+
+@pytest.fixture(autouse=True)
+def no_tune_table():
+    Q.tune_table_clear()
+    yield
+    Q.tune_table_clear()
+
+
+def wave(M, N, K, **kw):
+    return Q.launch_plan(M, N, K, **kw)["variant"] == 0
+
+
+def test_automatic_launch_is_reported(tmp_path):
+    p = Q.launch_plan(1024, 4096, 8192)
+    assert p["variant"] == 0 and p["tile_m"] % 16 == 0 and p["tile_n"] % 16 == 0
+    assert p["k_ranges"] in (1, 2, 4, 8) and p["launches"] == 1 + (p["split_k"] >= 4)
+    # where the rules stay with a nameable kernel it is the one select_config reports
+    for M, N, K in ((1, 4096, 4096), (16, 12288, 4096)):
+        p = Q.launch_plan(M, N, K)
+        assert {f: p[f] for f in ("variant", "split_k", "tile_m", "tile_n")} == Q.select_config(M, N, K)
+        assert p["k_ranges"] == 0 and p["launches"] == 1
+    # a recorded configuration, and the automatic choice recorded as such
+    t = tmp_path / "t.txt"
+    t.write_text("quick-tune 1\n1024 4096 8192 2 2 128 32\n512 4096 8192 0 0 0 0\n")
+    Q.tune_table_load(str(t))
+    assert Q.launch_plan(1024, 4096, 8192) == dict(variant=2, split_k=2, tile_m=128, tile_n=32, k_ranges=0,
+                                                   launches=2)
+    assert wave(512, 4096, 8192) and wave(1024, 4096, 8192, cfg=Q.make_config())
+
+
+def test_explicit_launch_is_the_configuration():
+    c = Q.make_config(variant=6, split_k=2, tile_m=64, tile_n=32)
+    assert Q.launch_plan(100, 4096, 4096, cfg=c) == dict(c.as_dict(), k_ranges=0, launches=2)
+    assert Q.launch_plan(100, 4096, 4096, cfg=Q.make_config(variant=2, split_k=1))["launches"] == 1
+    # the gated form pairs n-tiles: its stream kernel has two per wave
+    assert Q.launch_plan(1, 4096, 4096)["tile_n"] == 1 and Q.launch_plan(1, 4096, 4096, gated=True)["tile_n"] == 2
+
+
+def test_launch_plan_errors():
+    assert Q.launch_plan(0, 4096, 4096) == dict.fromkeys(
+        ("variant", "split_k", "tile_m", "tile_n", "k_ranges", "launches"), 0)
+    assert Q.grouped_launch_plan(0, 8, 4096, 4096)["launches"] == 0
+    L = Q.lib()
+    p = ctypes.byref(Q.QuickLaunch())
+    assert L.quick_launch_plan(1, 4096, 4096, None, 0, None) == Q.QUICK_ERR_INVALID_ARG
+    assert L.quick_launch_plan(1, 4096, 4000, None, 0, p) == Q.QUICK_ERR_SHAPE
+    assert L.quick_launch_plan(1 << 16, 32768, 128, None, 0, p) == Q.QUICK_ERR_SHAPE
+    assert L.quick_launch_plan(1, 4112, 4096, None, 1, p) == Q.QUICK_ERR_SHAPE            # gated: N % 32
+    bad = Q.make_config(variant=4)
+    assert L.quick_launch_plan(1, 4096, 4096, ctypes.byref(bad), 0, p) == Q.QUICK_ERR_INVALID_ARG
+    assert L.quick_grouped_launch_plan(8, 0, 4096, 4096, None, p) == Q.QUICK_ERR_SHAPE
+    assert L.quick_grouped_launch_plan(8, 4, 4096, 4096, None, None) == Q.QUICK_ERR_INVALID_ARG
+
+
+def test_grouped_launch_is_reported():
+    p = Q.grouped_launch_plan(1024, 8, 28672, 4096)
+    assert p["variant"] == 0 and p["split_k"] == 1 and p["launches"] == 1
+    p = Q.grouped_launch_plan(1024, 8, 28672, 4096, cfg=Q.make_config(variant=2, split_k=2, tile_m=64, tile_n=32))
+    assert p == dict(variant=2, split_k=2, tile_m=64, tile_n=32, k_ranges=0, launches=2)
+    # 512 experts x 2^25 columns: more tiles than a grid of the wave-split form
+    # holds, whatever their size, so the tiled kernel's resident workgroups run
+    assert Q.grouped_launch_plan(32, 512, 1 << 25, 128)["variant"] == Q.VARIANT_STREAMK
