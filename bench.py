@@ -46,34 +46,17 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-AUTO_KERNEL = "wave_stream_kernel"
-
-
 def selection(Q, p) -> dict:
-    """The plan of a point's launch; variant 0 where the launch is left to the
-    rules and runs in the wave-split form (recorded so in the tune table, or
-    more than 16 rows and no table)."""
-    if p["M"] > 16 and Q.tune_table_size() == 0:
-        return dict(variant=0, split_k=0, tile_m=0, tile_n=0)
-    return Q.select_config(p["M"], p["N"], p["K"])
-
-
-def fold_reductions(rows):
-    """Dispatches (id, kernel symbol, value) with each reduction pass that
-    follows a wave-split launch added to it: whether there is one is the
-    library's choice, so launch_sequence has no entry for it."""
-    out = []
-    for r in rows:
-        if out and "splitk_reduce_kernel" in r[1] and AUTO_KERNEL in out[-1][1]:
-            out[-1] = (out[-1][0], out[-1][1], out[-1][2] + r[2])
-        else:
-            out.append(r)
-    return out
+    """What the library launches for a point (variant 0: the wave-split form)."""
+    return Q.launch_plan(p["M"], p["N"], p["K"])
 
 
 def kernel_name(sel: dict) -> str:
     if sel["variant"] == 0:
-        return AUTO_KERNEL
+        name = "wave_split_kernel<%d,%d>" % (sel["tile_m"], sel["tile_n"])
+        if sel["split_k"] > 1:
+            name += "(S=%d)" % sel["split_k"] if sel["launches"] == 1 else "+splitk_reduce(S=%d)" % sel["split_k"]
+        return name
     if sel["variant"] == 1:
         return "stream_kernel<MT,%d,%d>" % (sel["tile_n"], sel["split_k"])
     if sel["variant"] == 5:
@@ -98,19 +81,28 @@ def launch_sequence(points):
     seq = []
     for p in points:
         sel = p["sel"]
-        if sel["variant"] in (0, 1):   # both symbols hold "stream_kernel<"
-            seq.append((p["kernel"], "stream_kernel<"))
+        if sel["variant"] == 0:
+            nw = 8 // sel["k_ranges"]
+            prefix = "wave_split_kernel<%d, %d, %d," % (sel["tile_m"] // 16, sel["tile_n"] // (16 * nw), nw)
+        elif sel["variant"] == 1:
+            prefix = "stream_kernel<"
         elif sel["variant"] == 5:
-            seq.append((p["kernel"], "kstream_kernel<%d>" % sel["tile_n"]))
+            prefix = "kstream_kernel<%d>" % sel["tile_n"]
         elif sel["variant"] in (6, 7):
-            seq.append((p["kernel"], "tiled32_kernel<%d, %d, false>" % (sel["tile_m"], sel["tile_n"])))
-            if sel["variant"] == 6 and sel["split_k"] > 1:
-                seq.append((None, "splitk_reduce_kernel"))
+            prefix = "tiled32_kernel<%d, %d, false>" % (sel["tile_m"], sel["tile_n"])
         else:
-            seq.append((p["kernel"], "tiled_kernel<%d, %d, 0, false, false>" % (sel["tile_m"], sel["tile_n"])))
-            if sel["variant"] == 2 and sel["split_k"] > 1:
-                seq.append((None, "splitk_reduce_kernel"))
+            prefix = "tiled_kernel<%d, %d, 0, false, false>" % (sel["tile_m"], sel["tile_n"])
+        seq.append((p["kernel"], prefix))
+        if sel["launches"] == 2:
+            seq.append((None, "splitk_reduce_kernel"))
     return seq
+
+
+def launched(name, prefix):
+    """Whether the kernel symbol `name`, as the profiler prints it, is the one
+    that starts with `prefix` (the namespace before it excluded, so that
+    stream_kernel is not found in kstream_kernel)."""
+    return "::" + prefix in name
 
 
 def read_counter_csv(path: str, counter: str):
@@ -141,7 +133,7 @@ def whole_repetitions(names, seq):
     dispatched kernel `names`."""
     reps = 0
     while (reps + 1) * len(seq) <= len(names) and all(
-            prefix in names[reps * len(seq) + i] for i, (_, prefix) in enumerate(seq)):
+            launched(names[reps * len(seq) + i], prefix) for i, (_, prefix) in enumerate(seq)):
         reps += 1
     return reps
 
@@ -150,9 +142,7 @@ def launch_points(points):
     """Index of the point each launch of launch_sequence(points) belongs to."""
     idx = []
     for i, p in enumerate(points):
-        idx.append(i)
-        if p["sel"]["variant"] in (2, 6) and p["sel"]["split_k"] > 1:
-            idx.append(i)   # its split-K reduction pass
+        idx += [i] * p["sel"]["launches"]   # with its split-K reduction pass
     return idx
 
 
@@ -177,8 +167,8 @@ def ingest_pmc(fetch_csv, write_csv, cal_fetch_csv, cal_write_csv, points, domin
     per = {}
     per_point = {}
     for name, path in (("FETCH_SIZE", fetch_csv), ("WRITE_SIZE", write_csv)):
-        ours = fold_reductions([r for r in read_counter_csv(path, name)
-                                if "anonymous namespace)::" in r[1] and "at::" not in r[1]])
+        ours = [r for r in read_counter_csv(path, name)
+                if "anonymous namespace)::" in r[1] and "at::" not in r[1]]
         # whole repetitions of the step's launch sequence from the start
         # (eager warm-up, graph replays, eager timing steps); the subset-graph
         # replays that follow are not used
@@ -251,7 +241,6 @@ def ingest_trace(trace_csv, points, dominant, out_md, command, run_log=""):
             rows.append((int(r["Dispatch_Id"]), r["Kernel_Name"],
                          (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) * 1e-3))
     rows.sort()
-    rows = fold_reductions(rows)
     # whole repetitions of the step from the start (eager warm-up, graph
     # replays, eager event steps); the subset-graph replays that follow are
     # not used
@@ -264,7 +253,7 @@ def ingest_trace(trace_csv, points, dominant, out_md, command, run_log=""):
     j = 0
     for rep in range(reps):
         for i, p in enumerate(points):
-            n = 2 if (p["sel"]["variant"] in (2, 6) and p["sel"]["split_k"] > 1) else 1
+            n = p["sel"]["launches"]
             for t in range(n):
                 per_point[i][rep] += rows[j + t][2]
             if p["kernel"] == dominant:
@@ -290,7 +279,7 @@ def ingest_trace(trace_csv, points, dominant, out_md, command, run_log=""):
     n_dom = sum(1 for p in points if p["kernel"] == dominant)
     dom_prefix = next(pre for b, pre in seq if b == dominant)
     k = j
-    while k < len(rows) and dom_prefix in rows[k][1]:
+    while k < len(rows) and launched(rows[k][1], dom_prefix):
         k += 1
     sub = [r[2] for r in rows[j:j + (k - j) // n_dom * n_dom]]
     small = [i for i, p in enumerate(points) if p["M"] <= 16]
@@ -376,7 +365,7 @@ def gemm_counters(csv_path, points, counters):
             continue
         d = disp.setdefault(int(r["Dispatch_Id"]), {"name": name, "dur": dur})
         d[r["Counter_Name"]] = d.get(r["Counter_Name"], 0.0) + float(r["Counter_Value"])
-    ids = [i for i, _, _ in fold_reductions([(i, disp[i]["name"], 0) for i in sorted(disp)])]
+    ids = sorted(disp)
     names = [disp[i]["name"] for i in ids]
     reps = whole_repetitions(names, seq)
     if reps == 0:
@@ -388,7 +377,7 @@ def gemm_counters(csv_path, points, counters):
             d = disp[ids[j]]   # the GEMM kernel itself (a split-K reduction follows it)
             for c in tuple(counters) + ("dur",):
                 acc[i].setdefault(c, []).append(d.get(c, 0.0))
-            j += 2 if (p["sel"]["variant"] in (2, 6) and p["sel"]["split_k"] > 1) else 1
+            j += p["sel"]["launches"]
     return reps, acc, copies
 
 
@@ -741,10 +730,8 @@ def moe(reps=20, sweep=True):
     for cfg in cfgs:
         t = timed(lambda: grouped(cfg), outs)
         if cfg is None:
-            sel = Q.grouped_select_config(R, 8, mats[0]["N"], mats[0]["K"])
-            name = "auto %s" % (sel,)
-            if sel["tile_m"] == 128:
-                name += " + remainders < 64 rows in 32x32 tiles"
+            sel = Q.grouped_launch_plan(R, 8, mats[0]["N"], mats[0]["K"])
+            name = "automatic: " + kernel_name(sel)
         else:
             name = "v%d split %d tile %dx%d" % (cfg.variant, cfg.split_k, cfg.tile_m, cfg.tile_n)
         diff = max(float((a.float() - b.float()).abs().max() / b.float().abs().max())

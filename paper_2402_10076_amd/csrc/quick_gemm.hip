@@ -2200,7 +2200,7 @@ __device__ __forceinline__ void wsplit_tile(const WsLds& lds, const uint16_t* x,
 // otherwise.
 template <int MTT, int NP, int NW, int RH, int DW, int MTB = 0>
 __global__ void __launch_bounds__(64 * kWsWaves)
-wave_stream_kernel(const uint16_t* x, const u4_t* pw, const uint16_t* ps, const uint32_t* pz, uint16_t* y, float* ws, int M,
+wave_split_kernel(const uint16_t* x, const u4_t* pw, const uint16_t* ps, const uint32_t* pz, uint16_t* y, float* ws, int M,
               int N, int K, int kgps, int n_mtiles, int n_cg, int S, GroupArgs ga, Epi epi)
 {
     constexpr bool GRP = MTB > 0;
@@ -3005,7 +3005,7 @@ void launch_wsplit_t(const WsplitPlan& wp, const uint16_t* x, const u4_t* pw, co
 {
     const int nm = ceil_div(M, MTT * 16), ncg = ceil_div(N / 16, NP * NW);
     const dim3 grid((unsigned)ceil_div((int64_t)nm * ncg * wp.split, 8) * 8);
-    hipLaunchKernelGGL((wave_stream_kernel<MTT, NP, NW, RH, DW>), grid, dim3(64 * kWsWaves), 0, st, x, pw, ps, pz, y, ws, M,
+    hipLaunchKernelGGL((wave_split_kernel<MTT, NP, NW, RH, DW>), grid, dim3(64 * kWsWaves), 0, st, x, pw, ps, pz, y, ws, M,
                        N, K, wp.kgps, nm, ncg, wp.split, GroupArgs{}, epi);
 }
 
@@ -3039,7 +3039,7 @@ void launch_wsplit_grp_t(const uint16_t* x, const u4_t* pw, const uint16_t* ps, 
     const int64_t nm = ((int64_t)ga.routed + (int64_t)ga.experts * (MTT * 16 - 1)) / (MTT * 16);
     const int ncg = ceil_div(N / 16, NP * NW);
     const dim3 grid((unsigned)ceil_div(nm * ncg, 8) * 8);
-    hipLaunchKernelGGL((wave_stream_kernel<MTT, NP, NW, RH, DW, MTB>), grid, dim3(64 * kWsWaves), 0, st, x, pw, ps, pz, y,
+    hipLaunchKernelGGL((wave_split_kernel<MTT, NP, NW, RH, DW, MTB>), grid, dim3(64 * kWsWaves), 0, st, x, pw, ps, pz, y,
                        (float*)nullptr, M, N, K, K / 128, 0, ncg, 1, ga, epi);
 }
 

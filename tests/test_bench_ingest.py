@@ -2,7 +2,8 @@
 laid out like the profiler's (a kernel trace; one counter pass) are mapped
 back onto the bench step's launch sequence, and every GEMM gets exactly the
 values planted for it, including split-K launches with their reduction pass
-and the runtime's and torch's kernels interleaved."""
+and the runtime's and torch's kernels interleaved: with the committed tune
+table, with a table that holds only some of the shapes, and with none."""
 import csv
 import os
 import re
@@ -23,13 +24,20 @@ PMC_FIELDS = ["Correlation_Id", "Dispatch_Id", "Agent_Id", "Queue_Id", "Process_
               "Accum_VGPR_Count", "SGPR_Count", "Counter_Name", "Counter_Value", "Start_Timestamp", "End_Timestamp"]
 
 
-@pytest.fixture(scope="module")
-def points():
-    Q.tune_table_load(os.path.join(os.path.dirname(Q.LIB_PATH), "tune_mi355x.txt"))
+@pytest.fixture(scope="module", params=["table", "part", "rules"])
+def points(request, tmp_path_factory):
+    Q.tune_table_clear()
+    table = os.path.join(os.path.dirname(Q.LIB_PATH), "tune_mi355x.txt")
+    if request.param == "part":
+        lines = open(table).read().splitlines()
+        table = str(tmp_path_factory.mktemp("tune") / "part.txt")
+        open(table, "w").write("\n".join(lines[:1] + [l for l in lines[1:] if l.split()[1] != "8192"]) + "\n")
+    if request.param != "rules":
+        Q.tune_table_load(table)
     try:
-        pts = bench.build_points([2, 5])
+        pts = bench.build_points([2, 3, 5])
         for p in pts:
-            p["sel"] = Q.select_config(p["M"], p["N"], p["K"])
+            p["sel"] = bench.selection(Q, p)
             p["kernel"] = bench.kernel_name(p["sel"])
             p["bytes"] = W.alg_bytes(p["M"], p["N"], p["K"])
             p["flops"] = W.flops(p["M"], p["N"], p["K"])
@@ -78,7 +86,7 @@ def test_trace_ingest_maps_every_gemm(points, tmp_path):
         w.writeheader()
         w.writerows(rows)
     out = tmp_path / "trace.md"
-    dominant = "tiled_kernel<128,32>"
+    dominant = max((p["kernel"] for p in points), key=[p["kernel"] for p in points].count)
     dom_us = bench.ingest_trace(str(path), points, dominant, str(out), "cmd")
     text = out.read_text()
     assert "%d repetitions" % reps in text
@@ -87,7 +95,7 @@ def test_trace_ingest_maps_every_gemm(points, tmp_path):
     for i, (p, line) in enumerate(zip(points, table)):
         cells = [c.strip() for c in line.strip("|").split("|")]
         assert cells[5] == p["kernel"]
-        red = 0.5 if (p["sel"]["variant"] in (2, 6) and p["sel"]["split_k"] > 1) else 0.0
+        red = 0.5 if p["sel"]["launches"] == 2 else 0.0
         mean = np.mean([i + 10.0 + 0.25 * r for r in range(reps)]) + red
         assert abs(float(cells[6]) - mean) < 0.006, (p["kernel"], cells[6], mean)
         assert abs(float(cells[7]) - (i + 10.0 + red)) < 0.006
@@ -119,10 +127,33 @@ def test_launch_sequence_names_and_reduction_passes(points):
     seq = bench.launch_sequence(points)
     owner = bench.launch_points(points)
     assert len(seq) == len(owner)
-    split = [i for i, p in enumerate(points) if p["sel"]["variant"] in (2, 6) and p["sel"]["split_k"] > 1]
+    split = [i for i, p in enumerate(points) if p["sel"]["launches"] == 2]
     assert len(seq) == len(points) + len(split)
     assert sum(1 for _, pre in seq if pre == "splitk_reduce_kernel") == len(split)
     for (name, pre), i in zip(seq, owner):
         if name is not None:
             assert name == points[i]["kernel"]
-            assert re.match(r"(stream_kernel<|kstream_kernel<\d>|tiled(32)?_kernel<\d+, \d+)", pre)
+            assert re.match(r"(stream_kernel<|kstream_kernel<\d>|tiled(32)?_kernel<\d+, \d+|"
+                            r"wave_split_kernel<\d, \d, \d,)", pre)
+
+
+def test_labels_are_the_kernels_that_run(points):
+    """Every label is the library's own plan; a launch of another kernel in
+    its place is not taken for it, also where one symbol ends like another."""
+    for p in points:
+        sel = Q.launch_plan(p["M"], p["N"], p["K"])
+        assert p["sel"] == sel
+        kind = {0: "wave_split_kernel", 1: "stream_kernel", 2: "tiled_kernel", 3: "tiled_kernel", 5: "kstream_kernel",
+                6: "tiled32_kernel", 7: "tiled32_kernel"}[sel["variant"]]
+        assert p["kernel"].startswith(kind + "<")
+    assert any(p["sel"]["variant"] == 0 and p["sel"]["launches"] == 2 for p in points)
+    names = ["stream_kernel<", "kstream_kernel<1>", "wave_split_kernel<4, 3, 4,", "wave_split_kernel<2, 4, 2,",
+             "tiled_kernel<128, 32, 0, false, false>", "tiled32_kernel<128, 32, false>", "splitk_reduce_kernel"]
+    for a in names:
+        assert [bench.launched(_symbol(a), b) for b in names] == [a == b for b in names]
+    seq = bench.launch_sequence(points)
+    good = [_symbol(pre) for _, pre in seq]
+    assert bench.whole_repetitions(good * 2, seq) == 2
+    for i, (_, pre) in enumerate(seq):
+        wrong = "stream_kernel<" if pre != "stream_kernel<" else "wave_split_kernel<4, 3, 4,"
+        assert bench.whole_repetitions(good[:i] + [_symbol(wrong)] + good[i + 1:], seq) == 0
