@@ -3108,12 +3108,21 @@ double wsplit_us(const WsShape& w, int64_t tiles, int64_t kg)
     return w.fixed + (double)((tiles + kWsCus - 1) / kWsCus - 1) * w.next + rounds * (double)kg * w.per_kg;
 }
 
-// M <= 16: whether the wave-split form (one 16-row block) is the faster one.
-// The stream kernel stages all of x in every workgroup: it wins while its
-// workgroups still run in one round (7B o-proj at M = 16: 5.7 against 7.2
-// us), and loses once few fit a compute unit (13B o-proj at M = 16, x past the
-// LDS: 13.1 against 8.4 us; 11008 x 9744 at M = 3, one workgroup per compute
-// unit in three rounds: 18.6 against 16.5 us).  The sliced stream kernel wins
+// M <= 16: whether the wave-split form (one 16-row block) is the faster one
+// (lines drawn from 3500 random shapes, both forms timed in turn).
+// The stream kernel stages all of x in every workgroup.  While its workgroups
+// run in one round, one a compute unit, it wins whatever the size of x (3 x
+// 27520 x 640 [M x K x N] 16.2 against 25.7 us, 4 x 21632 x 3408 15.6 against
+// 22.6), except with x past the LDS, 14 rows or more and a matrix so narrow that
+// few compute units share the reading of x from L2 (16 x 11136 x 384 12.7
+// against 10.2).  Beyond, it loses with x past the LDS (16 x 5120 x 5120 13.1
+// against 8.4; 285 workgroups on, 1.14 to 1.6 times).  With x in the LDS, one
+// workgroup a compute unit: from two full rounds on (1.06 to 2 times), from one
+// at 6 rows or more (1.0 to 1.3 times; fewer rows 4 x 12672 x 6432 14.3 against
+// 15.8).  Two a compute unit: from one full round of 512 on (3 x 11008 x 9744
+// 18.6 against 16.5; 453 workgroups 2 x 12032 x 7248 12.8 against 16.3), not at 2
+// rows (2 x 14592 x 31232 45.7 against 52.1).  More: never by enough to
+// matter below four rounds.  The sliced stream kernel wins
 // while its workgroups are a single round (12288 x 4096 at M = 10: 9.9
 // against 10.0 us; 15360 x 5120 at M = 16, 360 workgroups: 15.0 against 12.4
 // us).  The 16-row tiles win on the largest matrices where they fill their last
@@ -3132,10 +3141,12 @@ bool wsplit_small_m(int64_t M, int64_t N, int64_t K, const Plan& pl)
     if (pl.variant == kVariantKStream) return (int64_t)ks_groups(N, pl.wn) * pl.split > kWsCus;
     if (pl.variant != kVariantStream) return true;
     const size_t xb = (size_t)pl.split * stream_slice_bytes((int)M, (int)(K / 128), pl.split);
-    if (xb > kStreamLdsX) return true;
+    const int64_t wgs = (N / 16 + pl.wn - 1) / pl.wn;
+    if (xb > kStreamLdsX) return wgs > kWsCus || (M >= 14 && wgs <= kWsCus / 4);
     const size_t lds = xb + (pl.split > 1 ? (size_t)pl.split * pl.wn * 1024 : 0);
     const int64_t per_cu = (int64_t)((160 * 1024) / std::max<size_t>(lds, 1));
-    return per_cu <= 2 && (N / 16 + pl.wn - 1) / pl.wn > kWsCus * per_cu;
+    if (per_cu == 1) return wgs > 2 * kWsCus || (wgs > kWsCus && M >= 6);
+    return per_cu == 2 && M > 2 && wgs > 2 * kWsCus;
 }
 
 bool wsplit_plan(int64_t M, int64_t N, int64_t K, const Plan& pl, size_t ws_bytes, const Epi& epi, WsplitPlan* out)

@@ -69,3 +69,21 @@ def test_grouped_launch_is_reported():
     # 512 experts x 2^25 columns: more tiles than a grid of the wave-split form
     # holds, whatever their size, so the tiled kernel's resident workgroups run
     assert Q.grouped_launch_plan(32, 512, 1 << 25, 128)["variant"] == Q.VARIANT_STREAMK
+
+
+# Which form the automatic choice takes where the lines of its rules lie: (M,
+# N, K), sizes at which the other form was timed and is slower.
+STREAM = [(3, 640, 27520), (4, 3408, 21632), (13, 816, 15488), (16, 1056, 8192), (4, 6432, 12672), (2, 5392, 25728),
+          (2, 8192, 28672), (2, 7248, 12032), (2, 31232, 14592)]
+STREAM_LEFT = [(16, 384, 11136), (16, 5120, 5120), (3, 9744, 11008), (4, 4560, 19584), (8, 5536, 6272),
+               (2, 21504, 21760)]
+
+
+@pytest.mark.parametrize("M,N,K", STREAM)
+def test_few_rows_stay_with_the_stream_kernel(M, N, K):
+    assert Q.launch_plan(M, N, K)["variant"] == Q.VARIANT_STREAM
+
+
+@pytest.mark.parametrize("M,N,K", STREAM_LEFT)
+def test_few_rows_leave_the_stream_kernel(M, N, K):
+    assert Q.select_config(M, N, K)["variant"] == Q.VARIANT_STREAM and wave(M, N, K)
