@@ -3123,9 +3123,11 @@ double wsplit_us(const WsShape& w, int64_t tiles, int64_t kg)
 // 18.6 against 16.5; 453 workgroups 2 x 12032 x 7248 12.8 against 16.3), not at 2
 // rows (2 x 14592 x 31232 45.7 against 52.1).  More: never by enough to
 // matter below four rounds.  The sliced stream kernel wins
-// while its workgroups are a single round (12288 x 4096 at M = 10: 9.9
-// against 10.0 us; 15360 x 5120 at M = 16, 360 workgroups: 15.0 against 12.4
-// us).  The 16-row tiles win on the largest matrices where they fill their last
+// in one round of workgroups (10 x 4096 x 12288 9.9 against 10.0), with one K
+// slice (wide and short matrices: 16 x 256 x 53168 4.7 against 10.1, 16 x 640 x
+// 42448 6.8 against 9.9), and in rounds filled to three quarters (411 workgroups,
+// 10 x 5376 x 17504 15.7 against 18.1); it loses where the last round is emptier
+// (360 workgroups, 16 x 5120 x 15360 15.0 against 12.4).  The 16-row tiles win on the largest matrices where they fill their last
 // round of two workgroups per compute unit to three quarters (at M = 16, 57344 x
 // 8192, 448 of 512: 51.5 against 55.5 us, 152064 x 5120, 1188 of 1536: 88.6
 // against 97.8, 16384 x 28672 in 4 K slices, all 512: 53.2 against 55.3) and
@@ -3138,7 +3140,10 @@ bool wsplit_small_m(int64_t M, int64_t N, int64_t K, const Plan& pl)
         const int64_t wgs = (int64_t)ceil_div(N, kTiledWaves * pl.wn) * pl.split, slots = 2 * kWsCus;
         return wgs * 4 < (wgs + slots - 1) / slots * slots * 3;
     }
-    if (pl.variant == kVariantKStream) return (int64_t)ks_groups(N, pl.wn) * pl.split > kWsCus;
+    if (pl.variant == kVariantKStream) {
+        const int64_t wgs = (int64_t)ks_groups(N, pl.wn) * pl.split;
+        return pl.split > 1 && wgs > kWsCus && wgs * 4 < (wgs + kWsCus - 1) / kWsCus * kWsCus * 3;
+    }
     if (pl.variant != kVariantStream) return true;
     const size_t xb = (size_t)pl.split * stream_slice_bytes((int)M, (int)(K / 128), pl.split);
     const int64_t wgs = (N / 16 + pl.wn - 1) / pl.wn;

@@ -87,3 +87,18 @@ def test_few_rows_stay_with_the_stream_kernel(M, N, K):
 @pytest.mark.parametrize("M,N,K", STREAM_LEFT)
 def test_few_rows_leave_the_stream_kernel(M, N, K):
     assert Q.select_config(M, N, K)["variant"] == Q.VARIANT_STREAM and wave(M, N, K)
+
+
+SLICED = [(16, 53168, 256), (16, 42448, 640), (12, 37232, 896), (10, 17504, 5376), (10, 12288, 4096),
+          (16, 27648, 5120)]
+SLICED_LEFT = [(16, 15360, 5120), (16, 22016, 4096), (13, 12400, 4736)]
+
+
+@pytest.mark.parametrize("M,N,K", SLICED)
+def test_nine_rows_on_stay_with_the_sliced_kernel(M, N, K):
+    assert Q.launch_plan(M, N, K)["variant"] == Q.VARIANT_KSTREAM
+
+
+@pytest.mark.parametrize("M,N,K", SLICED_LEFT)
+def test_nine_rows_on_leave_the_sliced_kernel(M, N, K):
+    assert Q.select_config(M, N, K)["variant"] == Q.VARIANT_KSTREAM and wave(M, N, K)
