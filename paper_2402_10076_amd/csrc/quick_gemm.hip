@@ -3132,8 +3132,9 @@ double wsplit_us(const WsShape& w, int64_t tiles, int64_t kg)
 // 8192, 448 of 512: 51.5 against 55.5 us, 152064 x 5120, 1188 of 1536: 88.6
 // against 97.8, 16384 x 28672 in 4 K slices, all 512: 53.2 against 55.3) and
 // lose where they do not (73728 x 12288, 576 of 1024: 110 against 104; 35840 x
-// 8192 in 2 slices, 560 of 1024: 43.3 against 36.1) or are few and short (8192 x
-// 1152: 7.9 against 4.5).
+// 8192 in 2 slices, 560 of 1024: 43.3 against 36.1); smaller matrices lose on them
+// (8192 x 1152: 7.9 against 4.5) but for one or two k-groups, which do not fill
+// the wave-split form's K ranges (10 x 256 x 14240 [M x K x N] 4.0 against 4.9).
 bool wsplit_small_m(int64_t M, int64_t N, int64_t K, const Plan& pl)
 {
     if (pl.variant == kVariantTiled && K * N / 2 >= ((int64_t)128 << 20)) {
@@ -3144,7 +3145,7 @@ bool wsplit_small_m(int64_t M, int64_t N, int64_t K, const Plan& pl)
         const int64_t wgs = (int64_t)ks_groups(N, pl.wn) * pl.split;
         return pl.split > 1 && wgs > kWsCus && wgs * 4 < (wgs + kWsCus - 1) / kWsCus * kWsCus * 3;
     }
-    if (pl.variant != kVariantStream) return true;
+    if (pl.variant != kVariantStream) return K > 256;
     const size_t xb = (size_t)pl.split * stream_slice_bytes((int)M, (int)(K / 128), pl.split);
     const int64_t wgs = (N / 16 + pl.wn - 1) / pl.wn;
     if (xb > kStreamLdsX) return wgs > kWsCus || (M >= 14 && wgs <= kWsCus / 4);

@@ -102,3 +102,9 @@ def test_nine_rows_on_stay_with_the_sliced_kernel(M, N, K):
 @pytest.mark.parametrize("M,N,K", SLICED_LEFT)
 def test_nine_rows_on_leave_the_sliced_kernel(M, N, K):
     assert Q.select_config(M, N, K)["variant"] == Q.VARIANT_KSTREAM and wave(M, N, K)
+
+
+@pytest.mark.parametrize("M,N,K,form", [(10, 14240, 256, 2), (14, 8528, 256, 2), (9, 14240, 128, 2), (10, 14240, 384, 0)])
+def test_nine_rows_on_short_k(M, N, K, form):
+    assert Q.select_config(M, N, K)["variant"] == Q.VARIANT_TILED
+    assert Q.launch_plan(M, N, K)["variant"] == form
