@@ -2417,22 +2417,28 @@ namespace {
 using quick::tiled_resident;
 
 // The stream kernel's automatic shape.  Two n-tiles per wave for wide N from 3
-// rows on (one activation read serves both: 22016 x 4096 at M = 4 13.0 against
-// 13.7 us), one below (at M = 1 12.1 against 12.6 us, 27648 x 5120 16.8
-// against 17.7).  Four waves per workgroup (57344 x 8192 at M = 1 44.4 against
-// 46.9 us with two), eight while there are fewer than 2048 waves or to keep
-// each wave's range within the single pass of 16 units (8880 x 11008 at M = 1
-// 14.9 against 16.5 us); every wave keeps >= 2 k-groups.
+// rows on (one activation read serves both: 22016 x 4096 [N x K] at M = 4 13.0
+// against 13.7 us), one below (at M = 1 12.1 against 12.6 us, 27648 x 5120 16.8
+// against 17.7) unless K is short (fewer than 18 k-groups: 64048 x 1024 at M = 2
+// 8.9 against 11.1 with one; 23216 x 1152 5.7 against 6.0).  Four waves per
+// workgroup (57344 x 8192 at M = 1 44.4 against 46.9 us with two), eight while
+// there are fewer than 2048 waves or to keep each wave's range within the single
+// pass of 16 units (8880 x 11008 at M = 1 14.9 against 16.5 us); every wave keeps
+// >= 2 k-groups.  With a short K (from 3 rows on fewer than 11 k-groups) only as
+// many waves as 2048 in all need: a wave's few loads do not pay for its start
+// (40496 x 1152 at M = 7 8.5 with two, 9.1 us with four; 54592 x 1664 at M = 3
+// 12.7 and 12.1).
 void stream_defaults(int64_t M, int64_t N, int64_t K, Plan* pl)
 {
     const int64_t KG = K / 128;
     const int64_t NT = N / 16;
+    const bool short_k = KG < (M > 2 ? 11 : 18);
     pl->variant = kVariantStream;
-    pl->wn = NT / 2 >= 512 && M > 2 ? 2 : 1;
+    pl->wn = NT / 2 >= 512 && (M > 2 || short_k) ? 2 : 1;
     const int64_t wgs = (NT + pl->wn - 1) / pl->wn;
     int w = 1;
     while (w < 8 && KG / (2 * w) >= 2 &&
-           (w < 4 || wgs * w < 2048 || (KG > 16 * w && KG <= 128)))
+           (wgs * w < 2048 || (!short_k && (w < 4 || (KG > 16 * w && KG <= 128)))))
         w *= 2;
     pl->split = w;
     pl->bm = 0;

@@ -108,3 +108,12 @@ def test_nine_rows_on_leave_the_sliced_kernel(M, N, K):
 def test_nine_rows_on_short_k(M, N, K, form):
     assert Q.select_config(M, N, K)["variant"] == Q.VARIANT_TILED
     assert Q.launch_plan(M, N, K)["variant"] == form
+
+
+@pytest.mark.parametrize("M,N,K,waves,tiles", [
+    (2, 64048, 1024, 2, 2), (1, 30688, 1280, 4, 2), (2, 31568, 1664, 4, 2), (2, 23216, 1152, 4, 2),
+    (7, 40496, 1152, 2, 2), (6, 57968, 1280, 2, 2),                          # short K
+    (1, 57344, 8192, 4, 1), (1, 22016, 4096, 4, 1), (4, 22016, 4096, 4, 2), (3, 34320, 2304, 4, 2),
+    (1, 8880, 11008, 8, 1), (1, 4096, 4096, 8, 1)])
+def test_stream_kernel_shape(M, N, K, waves, tiles):
+    assert Q.select_config(M, N, K) == dict(variant=Q.VARIANT_STREAM, split_k=waves, tile_m=0, tile_n=tiles)
