@@ -3161,6 +3161,31 @@ bool wsplit_small_m(int64_t M, int64_t N, int64_t K, const Plan& pl)
     return per_cu == 2 && M > 2 && wgs > 2 * kWsCus;
 }
 
+// From 17 rows on: whether the tiled plan is the faster one.  The lines are
+// drawn from 7300 random shapes (17 <= M <= 2048, N from 256, K from 128), both
+// forms timed in turn; times in us are of M x K x N, the tiled kernel first.
+//  * 17 to 32 rows, tiles of 32 rows.  From 96 MB of weights on, with more
+//    than 1.5 workgroups for a compute unit, the tiled kernel streams them
+//    faster (26 x 11776 x 40192 69.9, 88.5; 28 x 23936 x 24352 77.1, 99.6; below,
+//    32 x 5120 x 27648 28.1, 25.1); so it does from 64 MB on where the
+//    wave-split form would take tiles of twice the rows (18 x 4864 x 35168 32.1,
+//    36.0).  Unsplit, nearly all of a round of two a compute unit (23 x 1920 x
+//    57712 17.7, 20.9).  From 32 MB on with no more than one workgroup a
+//    compute unit (19 x 23040 x 3904 18.7, 20.0).
+bool tiled_faster(int64_t M, int64_t N, int64_t K, const Plan& pl, const WsplitPlan& wp)
+{
+    if (pl.variant != kVariantTiled) return false;
+    const int64_t mb = K * N / 2 >> 20;
+    const int64_t wgs = (int64_t)ceil_div(M, pl.bm) * ceil_div(N, kTiledWaves * pl.wn) * pl.split;
+    if (M <= 32 && pl.bm == 32) {
+        if (mb >= 96 && wgs * 2 > kWsCus * 3) return true;
+        if (mb >= 64 && wp.mt >= 4) return true;
+        if (pl.split == 1 && wgs * 2 > kWsCus * 3 && wgs <= 2 * kWsCus) return true;
+        if (mb >= 32 && wgs <= kWsCus) return true;
+    }
+    return false;
+}
+
 bool wsplit_plan(int64_t M, int64_t N, int64_t K, const Plan& pl, size_t ws_bytes, const Epi& epi, WsplitPlan* out)
 {
     if (M <= 16 && !wsplit_small_m(M, N, K, pl)) return false;
@@ -3190,7 +3215,7 @@ bool wsplit_plan(int64_t M, int64_t N, int64_t K, const Plan& pl, size_t ws_byte
             }
         }
     }
-    return found;
+    return found && !(M > 16 && tiled_faster(M, N, K, pl, *out));
 }
 
 // The same for R routed rows over E experts, whose counts only the device

@@ -117,3 +117,18 @@ def test_nine_rows_on_short_k(M, N, K, form):
     (1, 8880, 11008, 8, 1), (1, 4096, 4096, 8, 1)])
 def test_stream_kernel_shape(M, N, K, waves, tiles):
     assert Q.select_config(M, N, K) == dict(variant=Q.VARIANT_STREAM, split_k=waves, tile_m=0, tile_n=tiles)
+
+
+TILED = [(26, 40192, 11776), (28, 24352, 23936), (32, 57344, 8192), (18, 35168, 4864), (23, 57712, 1920),
+         (19, 3904, 23040)]
+TILED_LEFT = [(27, 8816, 3840), (32, 12288, 4096), (33, 40192, 11776), (32, 27648, 5120)]
+
+
+@pytest.mark.parametrize("M,N,K", TILED)
+def test_more_rows_stay_with_the_tiled_kernel(M, N, K):
+    assert Q.launch_plan(M, N, K)["variant"] in (Q.VARIANT_TILED, Q.VARIANT_STREAMK)
+
+
+@pytest.mark.parametrize("M,N,K", TILED_LEFT)
+def test_more_rows_leave_the_tiled_kernel(M, N, K):
+    assert wave(M, N, K)
