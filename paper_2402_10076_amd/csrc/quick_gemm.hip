@@ -3172,11 +3172,16 @@ bool wsplit_small_m(int64_t M, int64_t N, int64_t K, const Plan& pl)
 //    36.0).  Unsplit, nearly all of a round of two a compute unit (23 x 1920 x
 //    57712 17.7, 20.9).  From 32 MB on with no more than one workgroup a
 //    compute unit (19 x 23040 x 3904 18.7, 20.0).
+//  * Stream-K plans that split at most 24 tiles past the whole rounds cost
+//    little more than those rounds (44 x 9472 x 33408, 261 tiles on 256
+//    workgroups, 64.3, 74.5; 242 x 10240 x 33024, 258, 170, 186; from 304 tiles on
+//    41 x 12544 x 38800 91.0, 88.8, and more with each).
 bool tiled_faster(int64_t M, int64_t N, int64_t K, const Plan& pl, const WsplitPlan& wp)
 {
+    const int64_t tiles = (int64_t)ceil_div(M, pl.bm) * ceil_div(N, kTiledWaves * pl.wn);
+    if (pl.variant == kVariantStreamK) return tiles > pl.split && tiles % pl.split <= 24;
     if (pl.variant != kVariantTiled) return false;
-    const int64_t mb = K * N / 2 >> 20;
-    const int64_t wgs = (int64_t)ceil_div(M, pl.bm) * ceil_div(N, kTiledWaves * pl.wn) * pl.split;
+    const int64_t mb = K * N / 2 >> 20, wgs = tiles * pl.split;
     if (M <= 32 && pl.bm == 32) {
         if (mb >= 96 && wgs * 2 > kWsCus * 3) return true;
         if (mb >= 64 && wp.mt >= 4) return true;

@@ -120,8 +120,8 @@ def test_stream_kernel_shape(M, N, K, waves, tiles):
 
 
 TILED = [(26, 40192, 11776), (28, 24352, 23936), (32, 57344, 8192), (18, 35168, 4864), (23, 57712, 1920),
-         (19, 3904, 23040)]
-TILED_LEFT = [(27, 8816, 3840), (32, 12288, 4096), (33, 40192, 11776), (32, 27648, 5120)]
+         (19, 3904, 23040), (44, 33408, 9472), (61, 33088, 8960), (242, 33024, 10240)]
+TILED_LEFT = [(27, 8816, 3840), (32, 12288, 4096), (33, 40192, 11776), (32, 27648, 5120), (41, 38800, 12544)]
 
 
 @pytest.mark.parametrize("M,N,K", TILED)
