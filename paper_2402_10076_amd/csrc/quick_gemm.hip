@@ -3176,8 +3176,19 @@ bool wsplit_small_m(int64_t M, int64_t N, int64_t K, const Plan& pl)
 //    little more than those rounds (44 x 9472 x 33408, 261 tiles on 256
 //    workgroups, 64.3, 74.5; 242 x 10240 x 33024, 258, 170, 186; from 304 tiles on
 //    41 x 12544 x 38800 91.0, 88.8, and more with each).
+//  * Short K, unsplit, in one round of tiles: the wave-split form's fixed cost
+//    counts, and its K ranges do not fill.  Tiles of 32 rows (a round is 512):
+//    up to 2 k-groups always (220 x 128 x 3504 3.3, 4.9), up to 5 and at 7 from
+//    129 tiles on (98 x 640 x 5120 6.2, 6.8; 64 tiles or fewer win by 1.2 to 1.7
+//    times), 6 from 193 to 256 (613 x 768 x 1328 6.8, 7.3; below 1.1 times), up to
+//    11 from 321 on (0.85 to 0.93 times; from 8 k-groups 321 tiles or fewer win).
+//    Tiles of 64 and 128 rows and 128 columns (256): up to 2 k-groups and at 3, 7,
+//    11 and 15, which the tiled kernel runs best for their length (43 x 128 x 24656
+//    4.2, 5.0; 1784 x 1408 x 1936 15.2, 16.5; 57 x 768 x 24000 10.0,
+//    8.5 the other way); with 128 rows up to 5 in a nearly full round (612 x 512 x 5744 9.3, 9.8).
 bool tiled_faster(int64_t M, int64_t N, int64_t K, const Plan& pl, const WsplitPlan& wp)
 {
+    const int64_t KG = K / 128;
     const int64_t tiles = (int64_t)ceil_div(M, pl.bm) * ceil_div(N, kTiledWaves * pl.wn);
     if (pl.variant == kVariantStreamK) return tiles > pl.split && tiles % pl.split <= 24;
     if (pl.variant != kVariantTiled) return false;
@@ -3188,6 +3199,11 @@ bool tiled_faster(int64_t M, int64_t N, int64_t K, const Plan& pl, const WsplitP
         if (pl.split == 1 && wgs * 2 > kWsCus * 3 && wgs <= 2 * kWsCus) return true;
         if (mb >= 32 && wgs <= kWsCus) return true;
     }
+    if (pl.bm == 32 && pl.split == 1 && tiles <= 2 * kWsCus)
+        return KG <= 2 || (tiles > 128 && (KG <= 5 || KG == 7)) || (tiles > 192 && tiles <= kWsCus && KG == 6) ||
+               (tiles > 320 && KG <= 11);
+    if (pl.wn == 16 && pl.split == 1 && tiles <= kWsCus)
+        return KG <= 2 || (KG <= 15 && KG % 4 == 3) || (pl.bm == 128 && tiles > 208 && KG <= 5);
     return false;
 }
 
