@@ -3186,6 +3186,10 @@ bool wsplit_small_m(int64_t M, int64_t N, int64_t K, const Plan& pl)
 //    11 and 15, which the tiled kernel runs best for their length (43 x 128 x 24656
 //    4.2, 5.0; 1784 x 1408 x 1936 15.2, 16.5; 57 x 768 x 24000 10.0,
 //    8.5 the other way); with 128 rows up to 5 in a nearly full round (612 x 512 x 5744 9.3, 9.8).
+//  * Fewer than 1024 columns and many rows: a narrow tile re-reads the
+//    activations, which are the larger operand then, more often (64 x 128 tiles
+//    against those of 64 x 96, 2026 x 2176 x 704 13.9, 16.9; ranges that copy for
+//    themselves, 1731 x 12544 x 576 46.7, 54.5).
 bool tiled_faster(int64_t M, int64_t N, int64_t K, const Plan& pl, const WsplitPlan& wp)
 {
     const int64_t KG = K / 128;
@@ -3199,6 +3203,8 @@ bool tiled_faster(int64_t M, int64_t N, int64_t K, const Plan& pl, const WsplitP
         if (pl.split == 1 && wgs * 2 > kWsCus * 3 && wgs <= 2 * kWsCus) return true;
         if (mb >= 32 && wgs <= kWsCus) return true;
     }
+    if (N < 1024 && ((M >= 1024 && pl.bm == 64 && pl.wn == 16 && pl.split == 1) || (M >= 1280 && wp.nw == 1)))
+        return true;
     if (pl.bm == 32 && pl.split == 1 && tiles <= 2 * kWsCus)
         return KG <= 2 || (tiles > 128 && (KG <= 5 || KG == 7)) || (tiles > 192 && tiles <= kWsCus && KG == 6) ||
                (tiles > 320 && KG <= 11);
