@@ -3089,10 +3089,9 @@ using quick::WsplitPlan;
 // of reading the weights at 4.2 TB/s.  Splitting K costs the traffic of its
 // fp32 partial sums and, from kWsReduceSplit slices on, a second launch.  On
 // those GEMMs the choice is on average 0.9 % (at most 7 %) slower than the best
-// shape, and 1.23 times as fast as the tiled kernels on their own rules (0.4 %
-// slower at worst; beyond them, at K = 28672, 2 % slower at 512 rows of N = 8192
-// and 1.5 % at 1024, 8 % faster at 2048).  A split uses no more workspace than
-// `ws_bytes`, what the tiled plan needs.
+// shape.  It compares the shapes with each other; where the tiled kernel is the
+// faster one is tiled_faster's.  A split uses no more workspace than `ws_bytes`,
+// what the tiled plan needs.
 struct WsShape {
     int mt, np, nw;
     float fixed, next, per_kg;
@@ -3190,6 +3189,9 @@ bool wsplit_small_m(int64_t M, int64_t N, int64_t K, const Plan& pl)
 //    activations, which are the larger operand then, more often (64 x 128 tiles
 //    against those of 64 x 96, 2026 x 2176 x 704 13.9, 16.9; ranges that copy for
 //    themselves, 1731 x 12544 x 576 46.7, 54.5).
+//  * The same tiles and K slices, up to 2 of them, from 48 k-groups on: the
+//    tiled kernel's loop is 1 to 5 % faster (512 x 28672 x 8192 about 2 %, 744 x
+//    22272 x 4848 154, 162; a shorter K 1 to 5 % slower, and so with more slices).
 bool tiled_faster(int64_t M, int64_t N, int64_t K, const Plan& pl, const WsplitPlan& wp)
 {
     const int64_t KG = K / 128;
@@ -3208,6 +3210,9 @@ bool tiled_faster(int64_t M, int64_t N, int64_t K, const Plan& pl, const WsplitP
     if (pl.bm == 32 && pl.split == 1 && tiles <= 2 * kWsCus)
         return KG <= 2 || (tiles > 128 && (KG <= 5 || KG == 7)) || (tiles > 192 && tiles <= kWsCus && KG == 6) ||
                (tiles > 320 && KG <= 11);
+    if (pl.bm == 16 * wp.mt && kTiledWaves * pl.wn == 16 * wp.np * wp.nw && wp.nw == kTiledWaves &&
+        pl.split == wp.split && pl.split <= 2 && KG >= 48)
+        return true;
     if (pl.wn == 16 && pl.split == 1 && tiles <= kWsCus)
         return KG <= 2 || (KG <= 15 && KG % 4 == 3) || (pl.bm == 128 && tiles > 208 && KG <= 5);
     return false;
