@@ -2424,23 +2424,29 @@ using quick::tiled_resident;
 // workgroup (57344 x 8192 at M = 1 44.4 against 46.9 us with two), eight while
 // there are fewer than 2048 waves or to keep each wave's range within the single
 // pass of 16 units (8880 x 11008 at M = 1 14.9 against 16.5 us); every wave keeps
-// >= 2 k-groups.  With a short K (from 3 rows on fewer than 11 k-groups) only as
-// many waves as 2048 in all need: a wave's few loads do not pay for its start
-// (40496 x 1152 at M = 7 8.5 with two, 9.1 us with four; 54592 x 1664 at M = 3
-// 12.7 and 12.1).
-void stream_defaults(int64_t M, int64_t N, int64_t K, Plan* pl)
+// >= 2 k-groups.  Where a wave has two n-tiles the single pass pays from 5 rows on
+// only, or from 2 with few columns (the gated form, `pairs`: 26624 x 12416 at M =
+// 2 39.0 with four waves, 44.2 with eight, 10912 x 9088 at M = 1 16.4 and 17.3;
+// 20000 columns or more at 3 and 4 rows 0.93 times on average).  With a short K
+// (from 3 rows on fewer than 11 k-groups) only as many waves as 2048 in all need: a
+// wave's few loads do not pay for its start (40496 x 1152 at M = 7 8.5 with two,
+// 9.1 us with four; 54592 x 1664 at M = 3 12.7 and 12.1).
+void stream_defaults(int64_t M, int64_t N, int64_t K, Plan* pl, bool pairs = false)
 {
     const int64_t KG = K / 128;
     const int64_t NT = N / 16;
     const bool short_k = KG < (M > 2 ? 11 : 18);
     pl->variant = kVariantStream;
     pl->wn = NT / 2 >= 512 && (M > 2 || short_k) ? 2 : 1;
+    const bool one_pass = KG <= 128 && ((pl->wn == 1 && !pairs) || M >= 5 || (M >= 2 && NT / 2 < 512));
     const int64_t wgs = (NT + pl->wn - 1) / pl->wn;
     int w = 1;
     while (w < 8 && KG / (2 * w) >= 2 &&
-           (wgs * w < 2048 || (!short_k && (w < 4 || (KG > 16 * w && KG <= 128)))))
+           (wgs * w < 2048 || (!short_k && (w < 4 || (KG > 16 * w && one_pass)))))
         w *= 2;
     pl->split = w;
+    pl->auto_waves = true;
+    if (pairs) pl->wn = 2;
     pl->bm = 0;
     pl->kgps = 0;
 }
@@ -2609,6 +2615,7 @@ int make_plan(int64_t M, int64_t N, int64_t K, const quick_config_t* cfg, Plan* 
             if (cfg->split_k != 1 && cfg->split_k != 2 && cfg->split_k != 4 && cfg->split_k != 8)
                 return QUICK_ERR_INVALID_ARG;
             pl->split = cfg->split_k;
+            pl->auto_waves = false;
         }
         if (cfg->tile_n) {
             if (cfg->tile_n != 1 && cfg->tile_n != 2) return QUICK_ERR_INVALID_ARG;
@@ -3332,12 +3339,13 @@ int validate(const void* x, const void* packed, const void* scales, const void* 
 // tiled kernel: an even number of 16-column tiles per wave) unless a split-K
 // reduction pass applies it.  Choices left automatic are adjusted; an
 // explicit one that conflicts (a tile_n the caller set) is an error.
-int epilogue_plan(const Epi& epi, const quick_config_t* cfg, Plan* pl)
+int epilogue_plan(int64_t M, int64_t N, int64_t K, const Epi& epi, const quick_config_t* cfg, Plan* pl)
 {
     if (!epi.act) return QUICK_OK;
     const bool fixed_n = cfg && cfg->tile_n;
     if ((pl->variant == kVariantStream || pl->variant == kVariantKStream) && pl->wn != 2) {
         if (fixed_n) return QUICK_ERR_INVALID_ARG;
+        if (pl->variant == kVariantStream && pl->auto_waves) stream_defaults(M, N, K, pl, true);
         pl->wn = 2;
     }
     if (is_tiled(pl->variant) && pl->wn == 16 && !(pl->variant == kVariantTiled && pl->split > 1)) {
@@ -3360,7 +3368,7 @@ int plan_launch(int64_t M, int64_t N, int64_t K, const quick_config_t* cfg, cons
 {
     int st = make_plan(M, N, K, cfg, &out->pl);
     if (st) return st;
-    st = epilogue_plan(epi, cfg, &out->pl);
+    st = epilogue_plan(M, N, K, epi, cfg, &out->pl);
     if (st || M == 0) return st;
     finish_plan(M, N, K, &out->pl);
     out->need = plan_workspace(M, N, out->pl);
@@ -4085,7 +4093,7 @@ extern "C" size_t quick_fused_workspace_bytes(int64_t M, int64_t N, int64_t K, c
     if (M <= 0 || N <= 0 || K <= 0 || K % 128 != 0 || N % 16 != 0) return 0;
     Plan pl;
     if (make_plan(M, N, K, cfg, &pl)) return 0;
-    if (epilogue_plan(to_epi(epi), cfg, &pl)) return 0;
+    if (epilogue_plan(M, N, K, to_epi(epi), cfg, &pl)) return 0;
     finish_plan(M, N, K, &pl);
     return plan_workspace(M, N, pl);
 }

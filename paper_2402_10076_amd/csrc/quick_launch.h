@@ -44,6 +44,7 @@ struct Plan {
     int bm;     // tiled: rows per workgroup
     int wn;     // tiled: columns per wave; stream kernels: n-tiles per wave
     int kgps;   // tiled split-K and sliced stream: k-groups per slice
+    bool auto_waves = false;   // stream: `split` is stream_defaults' choice
 };
 
 // A launch of the wave-split kernel.

@@ -138,3 +138,14 @@ def test_more_rows_stay_with_the_tiled_kernel(M, N, K):
 @pytest.mark.parametrize("M,N,K", TILED_LEFT)
 def test_more_rows_leave_the_tiled_kernel(M, N, K):
     assert wave(M, N, K)
+
+
+@pytest.mark.parametrize("M,N,K,waves", [(1, 26688, 10112, 4), (2, 26624, 12416, 4), (1, 10912, 9088, 4),
+                                         (3, 16384, 8448, 4), (2, 9056, 9088, 8), (6, 22784, 2176, 4)])
+def test_stream_kernel_shape_gated(M, N, K, waves):
+    """The waves are chosen for the pairs of n-tiles that the gated form has."""
+    p = Q.launch_plan(M, N, K, gated=True)
+    assert (p["variant"], p["split_k"], p["tile_n"]) == (Q.VARIANT_STREAM, waves, 2)
+    # set by the caller: kept
+    p = Q.launch_plan(M, N, K, gated=True, cfg=Q.make_config(variant=1, split_k=8))
+    assert (p["split_k"], p["tile_n"]) == (8, 2)
