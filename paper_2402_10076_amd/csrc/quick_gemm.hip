@@ -3120,6 +3120,8 @@ double wsplit_us(const WsShape& w, int64_t tiles, int64_t kg)
     return w.fixed + (double)((tiles + kWsCus - 1) / kWsCus - 1) * w.next + rounds * (double)kg * w.per_kg;
 }
 
+bool large_matrix(int64_t N, int64_t K) { return K * N / 2 >= ((int64_t)128 << 20); }
+
 // M <= 16: whether the wave-split form (one 16-row block) is the faster one
 // (lines drawn from 3500 random shapes, both forms timed in turn).
 // The stream kernel stages all of x in every workgroup.  While its workgroups
@@ -3147,9 +3149,11 @@ double wsplit_us(const WsShape& w, int64_t tiles, int64_t kg)
 // 8192 in 2 slices, 560 of 1024: 43.3 against 36.1); smaller matrices lose on them
 // (8192 x 1152: 7.9 against 4.5) but for one or two k-groups, which do not fill
 // the wave-split form's K ranges (10 x 256 x 14240 [M x K x N] 4.0 against 4.9).
+// The largest also lose where the wave-split form is left with tiles of 32 columns,
+// as the gated form is, which cannot take 48 (16 x 19968 x 16544 52.0 against 61.0).
 bool wsplit_small_m(int64_t M, int64_t N, int64_t K, const Plan& pl)
 {
-    if (pl.variant == kVariantTiled && K * N / 2 >= ((int64_t)128 << 20)) {
+    if (pl.variant == kVariantTiled && large_matrix(N, K)) {
         const int64_t wgs = (int64_t)ceil_div(N, kTiledWaves * pl.wn) * pl.split, slots = 2 * kWsCus;
         return wgs * 4 < (wgs + slots - 1) / slots * slots * 3;
     }
@@ -3254,7 +3258,9 @@ bool wsplit_plan(int64_t M, int64_t N, int64_t K, const Plan& pl, size_t ws_byte
             }
         }
     }
-    return found && !(M > 16 && tiled_faster(M, N, K, pl, *out));
+    if (!found) return false;
+    if (M <= 16) return !(pl.variant == kVariantTiled && large_matrix(N, K) && out->np == 2);
+    return !tiled_faster(M, N, K, pl, *out);
 }
 
 // The same for R routed rows over E experts, whose counts only the device

@@ -149,3 +149,8 @@ def test_stream_kernel_shape_gated(M, N, K, waves):
     # set by the caller: kept
     p = Q.launch_plan(M, N, K, gated=True, cfg=Q.make_config(variant=1, split_k=8))
     assert (p["split_k"], p["tile_n"]) == (8, 2)
+
+
+@pytest.mark.parametrize("M,N,K,form", [(16, 16544, 19968, 2), (12, 19136, 22912, 2), (13, 38528, 8448, 0)])
+def test_largest_matrices_gated(M, N, K, form):
+    assert wave(M, N, K) and Q.launch_plan(M, N, K, gated=True)["variant"] == form
