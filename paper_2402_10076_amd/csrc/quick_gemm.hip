@@ -3191,7 +3191,9 @@ bool wsplit_small_m(int64_t M, int64_t N, int64_t K, const Plan& pl)
 //    up to 2 k-groups always (220 x 128 x 3504 3.3, 4.9), up to 5 and at 7 from
 //    129 tiles on (98 x 640 x 5120 6.2, 6.8; 64 tiles or fewer win by 1.2 to 1.7
 //    times), 6 from 193 to 256 (613 x 768 x 1328 6.8, 7.3; below 1.1 times), up to
-//    11 from 321 on (0.85 to 0.93 times; from 8 k-groups 321 tiles or fewer win).
+//    11 from 321 on (0.85 to 0.93 times; from 8 k-groups 320 tiles or fewer win);
+//    with the gated epilogue 1, 2 from 129 tiles on, and up to 11 from 257 on (32 x
+//    1152 x 55296 13.0, 15.2; 41 x 640 x 12384 1.2 times the other way).
 //    Tiles of 64 and 128 rows and 128 columns (256): up to 2 k-groups and at 3, 7,
 //    11 and 15, which the tiled kernel runs best for their length (43 x 128 x 24656
 //    4.2, 5.0; 1784 x 1408 x 1936 15.2, 16.5; 57 x 768 x 24000 10.0,
@@ -3206,7 +3208,8 @@ bool wsplit_small_m(int64_t M, int64_t N, int64_t K, const Plan& pl)
 bool tiled_faster(int64_t M, int64_t N, int64_t K, const Plan& pl, const WsplitPlan& wp)
 {
     const int64_t KG = K / 128;
-    const int64_t tiles = (int64_t)ceil_div(M, pl.bm) * ceil_div(N, kTiledWaves * pl.wn);
+    // (tiles of 32 rows counted with 128 columns, also the gated form's of 256)
+    const int64_t tiles = (int64_t)ceil_div(M, pl.bm) * ceil_div(N, pl.bm == 32 ? 128 : kTiledWaves * pl.wn);
     if (pl.variant == kVariantStreamK) return tiles > pl.split && tiles % pl.split <= 24;
     if (pl.variant != kVariantTiled) return false;
     const int64_t mb = K * N / 2 >> 20, wgs = tiles * pl.split;
@@ -3218,6 +3221,8 @@ bool tiled_faster(int64_t M, int64_t N, int64_t K, const Plan& pl, const WsplitP
     }
     if (N < 1024 && ((M >= 1024 && pl.bm == 64 && pl.wn == 16 && pl.split == 1) || (M >= 1280 && wp.nw == 1)))
         return true;
+    if (pl.bm == 32 && pl.wn == 32 && pl.split == 1 && tiles <= 2 * kWsCus)
+        return KG == 1 || (tiles > 128 && KG == 2) || (tiles > kWsCus && KG <= 11);
     if (pl.bm == 32 && pl.split == 1 && tiles <= 2 * kWsCus)
         return KG <= 2 || (tiles > 128 && (KG <= 5 || KG == 7)) || (tiles > 192 && tiles <= kWsCus && KG == 6) ||
                (tiles > 320 && KG <= 11);

@@ -154,3 +154,9 @@ def test_stream_kernel_shape_gated(M, N, K, waves):
 @pytest.mark.parametrize("M,N,K,form", [(16, 16544, 19968, 2), (12, 19136, 22912, 2), (13, 38528, 8448, 0)])
 def test_largest_matrices_gated(M, N, K, form):
     assert wave(M, N, K) and Q.launch_plan(M, N, K, gated=True)["variant"] == form
+
+
+@pytest.mark.parametrize("M,N,K,form", [(32, 55296, 1152, 2), (32, 41696, 768, 2), (24, 55904, 3968, 2),
+                                        (41, 12384, 640, 0), (32, 22016, 4096, 0)])
+def test_more_rows_gated(M, N, K, form):
+    assert Q.launch_plan(M, N, K, gated=True)["variant"] == form
