@@ -3348,8 +3348,9 @@ int validate(const void* x, const void* packed, const void* scales, const void* 
 // The epilogue's constraints on a plan.  The gated form needs each gate
 // tile and its up tile in one wave (stream kernel: 2 n-tiles per wave;
 // tiled kernel: an even number of 16-column tiles per wave) unless a split-K
-// reduction pass applies it.  Choices left automatic are adjusted; an
-// explicit one that conflicts (a tile_n the caller set) is an error.
+// reduction pass applies it.  The automatic choice is adjusted, whatever plan
+// it has; a configuration that conflicts (a tile_n that the caller set, or
+// tiles of 64 rows or more whose columns it left to the rules) is an error.
 int epilogue_plan(int64_t M, int64_t N, int64_t K, const Epi& epi, const quick_config_t* cfg, Plan* pl)
 {
     if (!epi.act) return QUICK_OK;
@@ -3360,7 +3361,7 @@ int epilogue_plan(int64_t M, int64_t N, int64_t K, const Epi& epi, const quick_c
         pl->wn = 2;
     }
     if (is_tiled(pl->variant) && pl->wn == 16 && !(pl->variant == kVariantTiled && pl->split > 1)) {
-        if (fixed_n || pl->bm > 32) return QUICK_ERR_INVALID_ARG;
+        if (fixed_n || (pl->bm > 32 && cfg && !is_auto_config(*cfg))) return QUICK_ERR_INVALID_ARG;
         pl->wn = 32;
     }
     return QUICK_OK;

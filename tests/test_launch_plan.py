@@ -2,6 +2,7 @@
 (quick_launch_plan, quick_grouped_launch_plan): which sizes run in the
 wave-split form and which in a kernel that a configuration names."""
 import ctypes
+import os
 
 import pytest
 
@@ -160,3 +161,26 @@ def test_largest_matrices_gated(M, N, K, form):
                                         (41, 12384, 640, 0), (32, 22016, 4096, 0)])
 def test_more_rows_gated(M, N, K, form):
     assert Q.launch_plan(M, N, K, gated=True)["variant"] == form
+
+
+GATED = [(48, 28672, 4096), (64, 22016, 4096), (128, 12288, 4096), (256, 16384, 6144), (44, 33408, 9472),
+         (128, 10240, 8192)]
+
+
+@pytest.mark.parametrize("table", [False, True])
+@pytest.mark.parametrize("M,N,K", GATED)
+def test_automatic_gated_call_is_never_refused(M, N, K, table):
+    """The tiled plan of these sizes has 16-column waves on 64 or 128 rows,
+    which cannot pair a gate tile with its up tile: the automatic choice takes
+    another form, with the committed tune table and without, and only a
+    configuration that the caller names is refused."""
+    if table:
+        Q.tune_table_load(os.path.join(os.path.dirname(Q.LIB_PATH), "tune_mi355x.txt"))
+    else:
+        sel = Q.select_config(M, N, K)
+        assert sel["tile_m"] > 32 and sel["tile_n"] == 16
+    p = Q.launch_plan(M, N, K, gated=True)
+    assert p["variant"] == 0 or p["tile_n"] == 32
+    assert Q.launch_plan(M, N, K, gated=True, cfg=Q.make_config()) is not None
+    with pytest.raises(Q.QuickError):
+        Q.launch_plan(M, N, K, gated=True, cfg=Q.make_config(variant=2, split_k=1, tile_m=64, tile_n=16))

@@ -79,7 +79,7 @@ def test_automatic_form(M, N, K):
 
 
 @pytest.mark.parametrize("M,N,K", [(16, 12288, 512), (17, 32, 128), (33, 2048, 11008), (65, 672, 11008),
-                                   (97, 1056, 384), (129, 1632, 1152)])
+                                   (97, 1056, 384), (129, 1632, 1152), (48, 20512, 256), (128, 10272, 384)])
 def test_automatic_form_with_epilogues(M, N, K):
     """Bias, and bias with the gated SiLU (a gate tile and its up tile end up
     in one wave whatever the tile).  With h the GEMM's bound E: silu' <= 1.1,
