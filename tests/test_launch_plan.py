@@ -3,6 +3,7 @@
 wave-split form and which in a kernel that a configuration names."""
 import ctypes
 import os
+import re
 
 import pytest
 
@@ -184,3 +185,39 @@ def test_automatic_gated_call_is_never_refused(M, N, K, table):
     assert Q.launch_plan(M, N, K, gated=True, cfg=Q.make_config()) is not None
     with pytest.raises(Q.QuickError):
         Q.launch_plan(M, N, K, gated=True, cfg=Q.make_config(variant=2, split_k=1, tile_m=64, tile_n=16))
+
+
+def _source_shapes(name, lower):
+    """(rows, columns, K ranges[, rows of the lower tiles]) of the wave-split shapes in the library's source."""
+    src = open(os.path.join(os.path.dirname(Q.LIB_PATH), "csrc", "quick_gemm.hip")).read()
+    body = re.search(r"#define %s\(X\)(.*?[^\\])\n" % name, src, re.S).group(1)
+    rows = [[float(v.rstrip("f")) for v in m.split(",")] for m in re.findall(r"X\((.*?)\)", body)]
+    return {(int(16 * r[0]), int(16 * r[1] * r[2]), int(8 // r[2])) + ((int(16 * r[8]),) if lower else ())
+            for r in rows}
+
+
+def test_gpu_tests_run_every_wave_split_shape():
+    """The sizes of test_wave_split_gpu.py run every shape of the form; gated
+    ones and two K slices with each epilogue are among them; of the grouped
+    form the full-height and, where it has one, the lower tiles."""
+    import test_wave_split_gpu as t
+    plans = [Q.launch_plan(*s) for s in t.SIZES]
+    run = {(p["tile_m"], p["tile_n"], p["k_ranges"]) for p in plans if p["variant"] == 0}
+    assert run == _source_shapes("QUICK_WSPLIT_SHAPES", False)
+    assert {p["split_k"] for p in plans if p["variant"] == 0} >= {1, 2, 4, 8}
+    long_one_range = {(p["tile_m"], p["tile_n"]) for s, p in zip(t.SIZES, plans)
+                      if p["variant"] == 0 and p["k_ranges"] == 1 and s[2] // 128 >= 9}
+    assert long_one_range >= {(m, n) for m, n, k in run if k == 1 and (m, n) != (96, 512)}
+    for gated in (False, True):
+        assert any(p["variant"] == 0 and p["split_k"] == 2
+                   for p in (Q.launch_plan(*s, gated=gated) for s in t.EPILOGUES))
+    bodies = set()
+    for counts, N, K in t.GROUPS:
+        p = Q.grouped_launch_plan(sum(counts), len(counts), N, K)
+        for r in counts:
+            tile = p["tile_m"], p["tile_n"], p["k_ranges"]
+            bodies |= {tile + (-(-r // -(-r // tile[0])),)} if r else set()
+    for tm, tn, kr, low in _source_shapes("QUICK_WSPLIT_GRP_SHAPES", True):
+        rows = [b[3] for b in bodies if b[:3] == (tm, tn, kr)]
+        assert any(r > low for r in rows) or low == tm, (tm, tn, kr)
+        assert any(r <= low for r in rows), (tm, tn, kr)

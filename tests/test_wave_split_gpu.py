@@ -57,6 +57,14 @@ SIZES = [(3, 9744, 11008), (16, 5120, 5120), (9, 6144, 1024), (16, 12288, 512), 
          (449, 6576, 384), (1025, 6432, 384), (1025, 4944, 4224), (1347, 7312, 384), (1347, 9904, 384)]
 
 
+# ... chosen so that with the ones above every tile of the form runs (checked
+# without a GPU in test_launch_plan.py), those of one K range with an odd number
+# of k-groups that goes round the rings of weights and activations several times
+SIZES += [(17, 32, 1152), (17, 32, 5504), (97, 2736, 1152), (129, 5456, 1152), (225, 4112, 1152), (129, 4096, 1152),
+          (333, 8208, 1152), (449, 6544, 1152), (897, 8224, 1152), (513, 8080, 1152), (897, 8208, 1152),
+          (1347, 8848, 1152), (700, 9232, 1152), (1025, 9616, 1152), (1347, 9744, 1152)]
+
+
 @pytest.mark.parametrize("M,N,K", SIZES)
 def test_automatic_form(M, N, K):
     x, q, z, s = rand_case(M * 7 + N + K, M, K, N)
@@ -78,11 +86,16 @@ def test_automatic_form(M, N, K):
     assert torch.equal(p.gemm(xd), y)
 
 
-@pytest.mark.parametrize("M,N,K", [(16, 12288, 512), (17, 32, 128), (33, 2048, 11008), (65, 672, 11008),
-                                   (97, 1056, 384), (129, 1632, 1152), (48, 20512, 256), (128, 10272, 384)])
+EPILOGUES = [(16, 12288, 512), (17, 32, 128), (33, 2048, 11008), (65, 672, 11008),
+             (97, 1056, 384), (129, 1632, 1152), (48, 20512, 256), (128, 10272, 384),
+             (33, 2080, 5504), (65, 2080, 11008), (257, 6560, 1152), (700, 9248, 1152)]
+
+
+@pytest.mark.parametrize("M,N,K", EPILOGUES)
 def test_automatic_form_with_epilogues(M, N, K):
     """Bias, and bias with the gated SiLU (a gate tile and its up tile end up
-    in one wave whatever the tile).  With h the GEMM's bound E: silu' <= 1.1,
+    in one wave whatever the tile), with one K slice, with the reduction pass and
+    (33 and 65 rows) in the last of two slices to arrive.  With h the GEMM's bound E: silu' <= 1.1,
     |silu(g)| <= |g|, so the product moves by 1.1 E |u| + |g| E + 1.1 E^2 at most."""
     x, q, z, s = rand_case(M + 3 * N + K, M, K, N)
     b = np.random.Generator(np.random.PCG64(M)).uniform(-2, 2, N).astype(np.float16).view(np.uint16)
@@ -110,7 +123,10 @@ def test_automatic_form_with_epilogues(M, N, K):
 # just do not, rows that fill several tiles unevenly
 GROUPS = [((1, 0, 0), 32, 1152), ((0, 17, 16, 1, 33), 1040, 384), ((64, 65, 86), 1040, 1152), ((0, 2), 16, 640),
           ((129, 0, 469), 5952, 384), ((314, 600, 30), 5952, 384), ((97, 1003, 96), 7888, 384),
-          ((300, 81, 89), 8576, 1152), ((128, 1, 1199), 8752, 384)]
+          ((300, 81, 89), 8576, 1152), ((128, 1, 1199), 8752, 384),
+          # full and lower tiles of the other shapes
+          ((77, 32), 6544, 4096), ((1047, 12), 208, 1152), ((733, 31), 16, 384), ((1160, 26), 3232, 384),
+          ((219, 80), 16, 384), ((1120, 80), 4992, 1152)]
 
 
 @pytest.mark.parametrize("counts,N,K", GROUPS, ids=lambda v: "-".join(map(str, v)) if isinstance(v, tuple) else str(v))
