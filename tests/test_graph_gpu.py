@@ -67,10 +67,9 @@ def test_graph_replay_matches_eager():
 
 
 def test_graph_replay_grouped_and_fused():
-    """The grouped GEMM's automatic two-launch plan (128-row tiles, then
-    32-row tiles over short remainders, both stream-K) and a fused gated
-    epilogue, captured together after an eager warm-up and replayed with
-    eager work in between: every replay equals the eager outputs."""
+    """The grouped GEMM's automatic launch and its 128-row stream-K tiles, and a
+    fused gated epilogue, captured together after an eager warm-up and replayed
+    with eager work in between: every replay equals the eager outputs."""
     side = torch.cuda.Stream()
     g_np = np.random.Generator(np.random.PCG64(41))
     T, K, N, E = 300, 512, 256, 4
@@ -83,10 +82,13 @@ def test_graph_replay_grouped_and_fused():
     rows = torch.from_numpy(np.concatenate([np.sort(g_np.integers(0, T, c)) for c in counts]).astype(np.int32)).cuda()
     offsets = torch.from_numpy(np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)).cuda()
     R = int(sum(counts))
-    assert Q.grouped_select_config(R, E, N, K)["tile_m"] == 128
+    assert Q.grouped_launch_plan(R, E, N, K)["variant"] == 0
+    streamk = Q.make_config(variant=3, tile_m=128, tile_n=32)
+    assert Q.grouped_launch_plan(R, E, N, K, cfg=streamk)["variant"] == Q.VARIANT_STREAMK
     dw, ds, dz = Q.to_device(*Q.pack_experts(experts))
     x = to_dev_x(rand_case(42, T, K, 16)[0])
     yg = torch.empty((R, N), dtype=torch.float16, device="cuda")
+    ys = torch.empty((R, N), dtype=torch.float16, device="cuda")
     xf, qf, zf, sf = rand_case(43, 40, 640, 96)
     pf = Packed(qf, zf, sf)
     xfd = to_dev_x(xf)
@@ -94,22 +96,25 @@ def test_graph_replay_grouped_and_fused():
 
     def run_all():
         Q.grouped_gemm(x, offsets, dw, ds, dz, N, rows=rows, y=yg)
+        Q.grouped_gemm(x, offsets, dw, ds, dz, N, rows=rows, y=ys, cfg=streamk)
         Q.gemm_fused(xfd, pf.dw, pf.ds, pf.dz, 96, activation=Q.ACT_SILU_GATE, y=yf)
 
     with torch.cuda.stream(side):
         run_all()
     side.synchronize()
-    eager = [yg.clone(), yf.clone()]
+    eager = [yg.clone(), yf.clone(), ys.clone()]
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g, stream=side):
         run_all()
     for rep in range(3):
         yg.fill_(float("nan"))
+        ys.fill_(float("nan"))
         yf.fill_(float("nan"))
         torch.cuda.synchronize()
         g.replay()
         torch.cuda.synchronize()
-        assert torch.equal(yg, eager[0]) and torch.equal(yf, eager[1]), "replay %d differs" % rep
+        assert torch.equal(yg, eager[0]) and torch.equal(yf, eager[1]) and torch.equal(
+            ys, eager[2]), "replay %d differs" % rep
         Q.grouped_gemm(x, offsets, dw, ds, dz, N, rows=rows, cfg=Q.make_config(variant=2, split_k=2, tile_m=32,
                                                                                tile_n=16))
         torch.cuda.synchronize()

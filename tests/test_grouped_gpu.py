@@ -149,21 +149,20 @@ def test_grouped_streamk_deterministic_and_caller_workspace():
 
 
 @pytest.mark.parametrize("counts", [[130, 149, 111, 20, 257, 0, 128, 200], [129, 131, 127, 128]])
-def test_grouped_auto_full_height_two_parts(counts):
-    """The automatic plan for about 128 rows per expert runs as two launches
-    (128-row tiles over whole tiles and remainders of >= 64 rows, then 32-row
-    tiles over the short remainders): every row against the oracle, the
-    workspace query covering both launches, repeated calls identical."""
+def test_grouped_auto_full_height(counts):
+    """The automatic launch for about 128 rows per expert (each expert's rows
+    spread over its tiles, lower ones where they fit): every row against the
+    oracle, the same bits with a caller's workspace of the size asked for."""
     T, K, N = 400, 512, 256
     E = len(counts)
     experts = _experts(81, E, K, N)
     x, _, _, _ = rand_case(82, T, K, 16)
     rows, offsets = _routing(83, T, E, counts=counts)
     R = int(offsets[-1])
-    assert Q.grouped_select_config(R, E, N, K)["tile_m"] == 128
+    assert Q.grouped_launch_plan(R, E, N, K)["variant"] == 0
     G = Grouped(experts)
     xd = to_dev_x(x)
-    say("grouped two parts R=%d counts=%s" % (R, counts))
+    say("grouped full height R=%d counts=%s" % (R, counts))
     y0 = from_dev_y(G.run(xd, rows, offsets))
     nb = Q.grouped_workspace_bytes(R, E, N, K)
     ws = torch.zeros(nb // 4 + 1, dtype=torch.int32, device="cuda")

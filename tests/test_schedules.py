@@ -6,8 +6,9 @@
   configuration.
 * The index arithmetic of the persistent schedules, written out the way the
   kernels compute it: the stream-K schedule (whole rounds of tiles, then the
-  rest of tiles x k-groups split), the grouped form's per-expert tile table,
-  and the sliced stream kernel's slices.  Each must cover every unit exactly
+  rest of tiles x k-groups split), the tiled kernel's grouped per-expert tile
+  table, the wave-split form's (rows spread evenly over an expert's tiles), and
+  the sliced stream kernel's slices.  Each must cover every unit exactly
   once, give every shared tile a
   contiguous run of contributors whose partial-slot indices agree between
   writer and reader, and keep every access inside its buffer.  (These are the
@@ -114,22 +115,14 @@ def test_streamk_contributors_and_slots(tiles, KG, G):
     assert len(lasts) == len(set(lasts)) and all(0 <= w < G for w in lasts)
 
 
-def grouped_tiles(offsets, R, BM, nn, part=0, unit=128, keep=64):
-    """The grouped kernel's tile table (clamped offsets, the rows of this
-    launch's part, per-expert m-tile counts, prefix sums) and its tile ->
-    (expert, m0, mend, n-tile) map."""
+def grouped_tiles(offsets, R, BM, nn):
+    """The tiled kernel's grouped tile table (clamped offsets, per-expert
+    m-tile counts, prefix sums) and its tile -> (expert, m0, mend, n-tile) map."""
     E = len(offsets) - 1
     lo, hi, cum = [], [], [0]
     for e in range(E):
         a = min(max(offsets[e], 0), R)
         b = min(max(offsets[e + 1], a), R)
-        if part:
-            rem = (b - a) % unit
-            lead = b if rem >= keep else b - rem
-            if part == 1:
-                b = lead
-            else:
-                a = lead
         lo.append(a), hi.append(b), cum.append(cum[-1] + (b - a + BM - 1) // BM)
 
     def tile(t):
@@ -165,29 +158,55 @@ def test_grouped_tile_table_covers_every_row_once(counts, BM):
     assert np.all(seen == 1)
 
 
+def wave_split_grouped(offsets, R, BM, ncg):
+    """The grouped wave-split launch: per workgroup of the grid that has a tile
+    its (tile id, expert, m0, mend, column group)."""
+    E = len(offsets) - 1
+    lo, hi, cum = [], [], [0]
+    for e in range(E):
+        a = min(max(offsets[e], 0), R)
+        b = min(max(offsets[e + 1], a), R)
+        lo.append(a), hi.append(b), cum.append(cum[-1] + (b - a + BM - 1) // BM)
+    grid = -(-((R + E * (BM - 1)) // BM * ncg) // 8) * 8   # the host's, from its upper bound of m-tiles
+    tiles = cum[E] * ncg
+    per = (tiles + 7) >> 3
+    for b in range(grid):
+        t = (b & 7) * per + (b >> 3)
+        if (b >> 3) >= per or t >= tiles:
+            continue
+        x, y = 0, E
+        while y - x > 1:
+            mid = (x + y) // 2
+            if cum[mid] * ncg <= t:
+                x = mid
+            else:
+                y = mid
+        te = cum[x + 1] - cum[x]
+        cg, mi = divmod(t - cum[x] * ncg, te)
+        n = hi[x] - lo[x]
+        yield t, x, lo[x] + n * mi // te, lo[x] + n * (mi + 1) // te, cg
+
+
+@pytest.mark.parametrize("BM", [16, 48, 80, 128])
 @pytest.mark.parametrize("counts", [[130, 149, 111, 127, 132, 133, 122, 120], [20, 0, 257, 128, 200, 63, 64, 1],
-                                    [0, 0, 0], [300], [127, 129, 191, 192, 193]])
-def test_grouped_two_part_split_covers_every_row_once(counts):
-    """The automatic full-height grouped plan runs as two launches: 128-row
-    tiles over each expert's whole tiles (and a remainder of >= 64 rows),
-    then 32-row tiles over the short remainders.  Together they cover every
-    routed row once; the second part holds fewer than 64 rows per expert."""
+                                    [0, 0, 0], [300], [127, 129, 191, 192, 193], [1] * 70])
+def test_grouped_wave_split_covers_every_row_once(counts, BM):
+    """Every row of every column group runs in one tile of one workgroup, no
+    tile is empty or higher than BM rows, and an expert's tiles differ by at
+    most one row."""
     offsets = np.concatenate([[0], np.cumsum(counts)]).tolist()
     R = offsets[-1]
-    nn = 2
-    seen = np.zeros((max(R, 1), nn), np.int64)
-    for part, BM in ((1, 128), (2, 32)):
-        n_mt, tile = grouped_tiles(offsets, R, BM, nn, part=part)
-        per_expert = {}
-        for t in range(n_mt * nn):
-            e, m0, mend, nt = tile(t)
-            assert offsets[e] <= m0 < mend <= offsets[e + 1]
-            rows = min(m0 + BM, mend) - m0
-            seen[m0:m0 + rows, nt] += 1
-            per_expert[e] = per_expert.get(e, 0) + rows
-        if part == 2:
-            assert all(v < 2 * 64 for v in per_expert.values())     # nn n-tiles x < 64 rows
+    ncg = 3
+    seen = np.zeros((max(R, 1), ncg), np.int64)
+    ids, heights = set(), {}
+    for t, e, m0, mend, cg in wave_split_grouped(offsets, R, BM, ncg):
+        assert t not in ids
+        ids.add(t)
+        assert offsets[e] <= m0 < mend <= offsets[e + 1] and mend - m0 <= BM and cg < ncg
+        heights.setdefault(e, set()).add(mend - m0)
+        seen[m0:mend, cg] += 1
     assert np.all(seen[:R] == 1)
+    assert all(max(h) - min(h) <= 1 for h in heights.values())
 
 
 def test_grouped_tile_table_clamps_malformed_offsets():
@@ -198,6 +217,8 @@ def test_grouped_tile_table_clamps_malformed_offsets():
         for t in range(n_mt * nn):
             e, m0, mend, nt = tile(t)
             assert 0 <= m0 < mend <= R
+        for _, _, m0, mend, _ in wave_split_grouped(offsets, R, BM, nn):
+            assert 0 <= m0 < mend <= R and mend - m0 <= BM
 
 
 def kstream_partition(M, N, K, npw, split):
