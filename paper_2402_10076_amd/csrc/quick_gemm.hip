@@ -3187,17 +3187,18 @@ bool wsplit_small_m(int64_t M, int64_t N, int64_t K, const Plan& pl)
 //    workgroups, 64.3, 74.5; 242 x 10240 x 33024, 258, 170, 186; from 304 tiles on
 //    41 x 12544 x 38800 91.0, 88.8, and more with each).
 //  * Short K, unsplit, in one round of tiles: the wave-split form's fixed cost
-//    counts, and its K ranges do not fill.  Tiles of 32 rows (a round is 512):
-//    up to 2 k-groups always (220 x 128 x 3504 3.3, 4.9), up to 5 and at 7 from
-//    129 tiles on (98 x 640 x 5120 6.2, 6.8; 64 tiles or fewer win by 1.2 to 1.7
-//    times), 6 from 193 to 256 (613 x 768 x 1328 6.8, 7.3; below 1.1 times), up to
-//    11 from 321 on (0.85 to 0.93 times; from 8 k-groups 320 tiles or fewer win);
-//    with the gated epilogue 1, 2 from 129 tiles on, and up to 11 from 257 on (32 x
-//    1152 x 55296 13.0, 15.2; 41 x 640 x 12384 1.2 times the other way).
-//    Tiles of 64 and 128 rows and 128 columns (256): up to 2 k-groups and at 3, 7,
-//    11 and 15, which the tiled kernel runs best for their length (43 x 128 x 24656
-//    4.2, 5.0; 1784 x 1408 x 1936 15.2, 16.5; 57 x 768 x 24000 10.0,
-//    8.5 the other way); with 128 rows up to 5 in a nearly full round (612 x 512 x 5744 9.3, 9.8).
+//    counts, and its K ranges do not fill.  Up to 2 k-groups always (220 x 128 x
+//    3504 3.3, 4.9).  Beyond, where its tile is the tiled kernel's (7/8 as tall
+//    and as wide), else it wins (141 x 640 x 3264 on 32 x 64 tiles 6.0, 5.2).  Of
+//    32 rows, from 129 tiles on (a round is 512): up to 5 k-groups and 7 (98 x 640
+//    x 5120 6.2, 6.8; 6 is even), from 321 tiles on up to 11 (0.85 to 0.93 times),
+//    3 whatever the tile, and 64 x 192 up to 7 (0.9 to 0.98 times).  Of 64 and 128
+//    rows (a round is 256): 3, 7 and 11, which the tiled kernel runs best for their
+//    length (43 x 896 x 24656 0.96 times, 1784 x 1408 x 1936 15.2, 16.5; 57 x 768 x
+//    24000 10.0, 8.5 the other way), of 128 rows 4 and 5 too (612 x 512 x 5744 9.3,
+//    9.8).  With the gated epilogue 32-row tiles of 1 k-group, 2 from 129 tiles on,
+//    and up to 11 from 257 on (32 x 1152 x 55296 13.0, 15.2; 41 x 640 x 12384 1.2
+//    times the other way).
 //  * Fewer than 1024 columns and many rows: a narrow tile re-reads the
 //    activations, which are the larger operand then, more often (64 x 128 tiles
 //    against those of 64 x 96, 2026 x 2176 x 704 13.9, 16.9; ranges that copy for
@@ -3223,14 +3224,15 @@ bool tiled_faster(int64_t M, int64_t N, int64_t K, const Plan& pl, const WsplitP
         return true;
     if (pl.bm == 32 && pl.wn == 32 && pl.split == 1 && tiles <= 2 * kWsCus)
         return KG == 1 || (tiles > 128 && KG == 2) || (tiles > kWsCus && KG <= 11);
+    const bool same_tile = 16 * wp.np * wp.nw == 128 && 8 * 16 * wp.mt >= 7 * pl.bm && 16 * wp.mt <= pl.bm;
     if (pl.bm == 32 && pl.split == 1 && tiles <= 2 * kWsCus)
-        return KG <= 2 || (tiles > 128 && (KG <= 5 || KG == 7)) || (tiles > 192 && tiles <= kWsCus && KG == 6) ||
-               (tiles > 320 && KG <= 11);
+        return KG <= 2 || (tiles > 128 && (KG == 3 || (same_tile && (KG <= 5 || KG == 7)))) ||
+               (tiles > 320 && KG <= 11) || (wp.mt == 4 && wp.np * wp.nw == 12 && KG <= 7);
     if (pl.bm == 16 * wp.mt && kTiledWaves * pl.wn == 16 * wp.np * wp.nw && wp.nw == kTiledWaves &&
         pl.split == wp.split && pl.split <= 2 && KG >= 48)
         return true;
     if (pl.wn == 16 && pl.split == 1 && tiles <= kWsCus)
-        return KG <= 2 || (KG <= 15 && KG % 4 == 3) || (pl.bm == 128 && tiles > 208 && KG <= 5);
+        return KG <= 2 || (same_tile && ((KG <= 11 && KG % 4 == 3) || (pl.bm == 128 && KG <= 5)));
     return false;
 }
 
