@@ -3177,7 +3177,8 @@ bool wsplit_small_m(int64_t M, int64_t N, int64_t K, const Plan& pl)
 //  * 17 to 32 rows, tiles of 32 rows.  From 96 MB of weights on, with more
 //    than 1.5 workgroups for a compute unit, the tiled kernel streams them
 //    faster (26 x 11776 x 40192 69.9, 88.5; 28 x 23936 x 24352 77.1, 99.6; below,
-//    32 x 5120 x 27648 28.1, 25.1); so it does from 64 MB on where the
+//    32 x 5120 x 27648 28.1, 25.1; not gated in 2 slices, 24 x 6144 x 35584 41.0,
+//    39.1, 30 x 6528 x 42496 46.1, 43.4); so it does from 64 MB on where the
 //    wave-split form would take tiles of twice the rows (18 x 4864 x 35168 32.1,
 //    36.0).  Unsplit, nearly all of a round of two a compute unit (23 x 1920 x
 //    57712 17.7, 20.9).  From 32 MB on with no more than one workgroup a
@@ -3206,7 +3207,7 @@ bool wsplit_small_m(int64_t M, int64_t N, int64_t K, const Plan& pl)
 //  * The same tiles and K slices, up to 2 of them, from 48 k-groups on: the
 //    tiled kernel's loop is 1 to 5 % faster (512 x 28672 x 8192 about 2 %, 744 x
 //    22272 x 4848 154, 162; a shorter K 1 to 5 % slower, and so with more slices).
-bool tiled_faster(int64_t M, int64_t N, int64_t K, const Plan& pl, const WsplitPlan& wp)
+bool tiled_faster(int64_t M, int64_t N, int64_t K, const Plan& pl, const WsplitPlan& wp, bool gated)
 {
     const int64_t KG = K / 128;
     // (tiles of 32 rows counted with 128 columns, also the gated form's of 256)
@@ -3215,7 +3216,7 @@ bool tiled_faster(int64_t M, int64_t N, int64_t K, const Plan& pl, const WsplitP
     if (pl.variant != kVariantTiled) return false;
     const int64_t mb = K * N / 2 >> 20, wgs = tiles * pl.split;
     if (M <= 32 && pl.bm == 32) {
-        if (mb >= 96 && wgs * 2 > kWsCus * 3) return true;
+        if (mb >= 96 && wgs * 2 > kWsCus * 3 && !(gated && pl.split == 2)) return true;
         if (mb >= 64 && wp.mt >= 4) return true;
         if (pl.split == 1 && wgs * 2 > kWsCus * 3 && wgs <= 2 * kWsCus) return true;
         if (mb >= 32 && wgs <= kWsCus) return true;
@@ -3267,7 +3268,7 @@ bool wsplit_plan(int64_t M, int64_t N, int64_t K, const Plan& pl, size_t ws_byte
     }
     if (!found) return false;
     if (M <= 16) return !(pl.variant == kVariantTiled && large_matrix(N, K) && out->np == 2);
-    return !tiled_faster(M, N, K, pl, *out);
+    return !tiled_faster(M, N, K, pl, *out, epi.act != 0);
 }
 
 // The same for R routed rows over E experts, whose counts only the device

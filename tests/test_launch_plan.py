@@ -160,7 +160,8 @@ def test_largest_matrices_gated(M, N, K, form):
 
 
 @pytest.mark.parametrize("M,N,K,form", [(32, 55296, 1152, 2), (32, 41696, 768, 2), (24, 55904, 3968, 2),
-                                        (41, 12384, 640, 0), (32, 22016, 4096, 0)])
+                                        (41, 12384, 640, 0), (32, 22016, 4096, 0), (24, 35584, 6144, 0),
+                                        (30, 42496, 6528, 0), (24, 12992, 22016, 2)])
 def test_more_rows_gated(M, N, K, form):
     assert Q.launch_plan(M, N, K, gated=True)["variant"] == form
 
