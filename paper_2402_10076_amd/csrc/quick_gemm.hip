@@ -3183,10 +3183,11 @@ bool wsplit_small_m(int64_t M, int64_t N, int64_t K, const Plan& pl)
 //    36.0).  Unsplit, nearly all of a round of two a compute unit (23 x 1920 x
 //    57712 17.7, 20.9).  From 32 MB on with no more than one workgroup a
 //    compute unit (19 x 23040 x 3904 18.7, 20.0).
-//  * Stream-K plans that split at most 24 tiles past the whole rounds cost
-//    little more than those rounds (44 x 9472 x 33408, 261 tiles on 256
-//    workgroups, 64.3, 74.5; 242 x 10240 x 33024, 258, 170, 186; from 304 tiles on
-//    41 x 12544 x 38800 91.0, 88.8, and more with each).
+//  * Stream-K plans of 64-row tiles that split at most 24 of them past the whole
+//    rounds cost little more than those rounds (44 x 9472 x 33408, 261 tiles on
+//    256 workgroups, 64.3, 74.5; from 304 tiles on 41 x 12544 x 38800 91.0, 88.8,
+//    and more with each).  Not those of 128 rows: a decoder layer of 1448 rows, its
+//    down projection 15872 x 5760 on 276 tiles, 947, 905.
 //  * Short K, unsplit, in one round of tiles: the wave-split form's fixed cost
 //    counts, and its K ranges do not fill.  Up to 2 k-groups always (220 x 128 x
 //    3504 3.3, 4.9).  Beyond, where its tile is the tiled kernel's (7/8 as tall
@@ -3212,7 +3213,7 @@ bool tiled_faster(int64_t M, int64_t N, int64_t K, const Plan& pl, const WsplitP
     const int64_t KG = K / 128;
     // (tiles of 32 rows counted with 128 columns, also the gated form's of 256)
     const int64_t tiles = (int64_t)ceil_div(M, pl.bm) * ceil_div(N, pl.bm == 32 ? 128 : kTiledWaves * pl.wn);
-    if (pl.variant == kVariantStreamK) return tiles > pl.split && tiles % pl.split <= 24;
+    if (pl.variant == kVariantStreamK) return pl.bm == 64 && tiles > pl.split && tiles % pl.split <= 24;
     if (pl.variant != kVariantTiled) return false;
     const int64_t mb = K * N / 2 >> 20, wgs = tiles * pl.split;
     if (M <= 32 && pl.bm == 32) {
