@@ -1772,9 +1772,10 @@ tiled32_kernel(const uint16_t* __restrict__ x, const u4_t* __restrict__ pw,
 
 #if QUICK_WSPLIT || QUICK_WSPLIT_GRP
 // ---------------------------------------------------------------------------
-// Wave-split kernel: the automatic form of the plain GEMM from 17 rows on (from
-// 9 where the stream kernels' grids do not fit the chip, see wsplit_small_m) and
-// of the grouped GEMM.
+// Wave-split kernel: the automatic form of the plain GEMM from 17 rows on where
+// the tiled kernel is not the faster one (see tiled_faster), below where the
+// stream kernels' grids do not fit the chip (from 2 rows on, see
+// wsplit_small_m), and of the grouped GEMM.
 //
 // What bounds it.  Up to about 300 rows it is the traffic into the compute
 // units, not the matrix cores: a tile of BM rows takes in BM * 256 bytes of
@@ -1819,12 +1820,13 @@ tiled32_kernel(const uint16_t* __restrict__ x, const u4_t* __restrict__ pw,
 // rows fit MTB blocks runs the lower body, so a remainder does not cost a
 // full-height tile.
 //
-// Measured against the tiled kernels on their own rules (us for one pass over
-// the layers of a block): 13B at 333 rows with bias 294 -> 240, 7B at 64 rows 143
-// -> 133, at 256 rows 137 -> 128 and at 2048 rows 764 -> 716, 70B at 128 rows 245
-// -> 238 and at 1024 rows 1485 -> 1475, 13B at 16 rows (against the stream
-// kernels) 145 -> 120; eight experts' feed-forward with 512 tokens 478 -> 434,
-// with 20 tokens 172 -> 153.
+// Measured against the other kernels alone (us for one pass over the layers of
+// a block, both sides in turn): 13B at 333 rows with bias 282 -> 236, 7B at 64
+// rows 144 -> 133, at 256 rows 133 -> 125 and at 2048 rows 733 -> 700, 70B at 128
+// rows 238, 238 and at 1024 rows 1429 -> 1400, 13B at 16 rows 145 -> 119; eight
+// experts' feed-forward with 512 tokens 459 -> 431, with 20 tokens 172 -> 152.
+// Over 700 random linear and decoder layers of 1 to 2048 rows 1.19 times as
+// fast; the slowest 0.95 times (96 x 896 x 23216 [M x K x N] 10.5 -> 11.0).
 //
 // Tried and slower: fragments loaded straight from L2 (16 bytes per clock);
 // workgroups of 4 waves; rings of 8 slots; K ranges starting at different
@@ -3096,7 +3098,8 @@ using quick::WsplitPlan;
 // of reading the weights at 4.2 TB/s.  Splitting K costs the traffic of its
 // fp32 partial sums and, from kWsReduceSplit slices on, a second launch.  On
 // those GEMMs the choice is on average 0.9 % (at most 7 %) slower than the best
-// shape.  It compares the shapes with each other; where the tiled kernel is the
+// shape.  It is no time: the launches of a decoder layer take 9 to 25 % more than
+// their estimates together.  It compares the shapes with each other; where the tiled kernel is the
 // faster one is tiled_faster's.  A split uses no more workspace than `ws_bytes`,
 // what the tiled plan needs.
 struct WsShape {
@@ -3109,6 +3112,7 @@ constexpr WsShape kWsShapes[] = {
 #undef QUICK_WS
 };
 constexpr int kWsCus = 256;
+static_assert(kWsCus <= kSkMaxWorkgroups, "one arrival counter per tile of a split launch, at most 2 kWsCus / 2");
 // a grid holds at most 2^32 - 1 work-items (512 a workgroup)
 constexpr int64_t kWsMaxTiles = ((int64_t)1 << 23) - 16;
 
@@ -3252,8 +3256,8 @@ bool wsplit_plan(int64_t M, int64_t N, int64_t K, const Plan& pl, size_t ws_byte
         if (tiles > kWsMaxTiles) continue;
         for (int s = 1; s <= 8; s *= 2) {
             const int64_t part = (int64_t)s * M * N * 4;
-            if (s > 1 && (KG / s < 4 || tiles * s > 2 * kWsCus || tiles > kSkMaxWorkgroups ||
-                          kSkCounterBytes + part > ws_bytes || part >= ((int64_t)1 << 32)))
+            if (s > 1 && (KG / s < 4 || tiles * s > 2 * kWsCus || kSkCounterBytes + part > ws_bytes ||
+                          part >= ((int64_t)1 << 32)))
                 break;
             const int kgps = ceil_div(KG, s);
             double us = wsplit_us(w, tiles * s, kgps);
@@ -3275,9 +3279,14 @@ bool wsplit_plan(int64_t M, int64_t N, int64_t K, const Plan& pl, size_t ws_byte
 // The same for R routed rows over E experts, whose counts only the device
 // knows: taken to spread about the mean as under uniform routing (standard
 // deviation sqrt(mean)), each expert's rows going evenly over its tiles, on
-// lower tiles where they fit those.  (Fitted to 38 grouped GEMMs, 4 to 16 experts
-// and 2 to 350 rows each: the choice is on average 1.3 %, at most 13 %, slower
-// than the best shape.)
+// lower tiles where they fit those.  Fitted to 38 grouped GEMMs, 4 to 16 experts
+// and 2 to 350 rows each.  Over 200 others of 4 to 64 experts and 8 to 2048 rows
+// the choice is on average 3 % slower than the best shape and 1.35 times as fast
+// as the tiled kernel's stream-K tiles (6 of 200 slower, to 0.89 times), and as
+// much so with experts drawn unequally (Zipf: 13 slower, to 0.75; one expert with
+// three quarters of the rows: 18, to 0.65, where a tile more per expert than
+// planned starts another round).  Planning for a wider spread loses more on
+// uniform routing (1.33 times) than it saves on the others.
 struct WsGrpShape {
     WsShape hi, lo;
 };
